@@ -94,7 +94,10 @@ typedef enum { LHF_FP64 = 0, LHF_FP32 = 1 } lhf_precision;
                                   not built, rejected with LHF_ERR_UNSUPPORTED */
 
 /* M2L kernel (lhf_desc.m2l_kernel).  AUTO picks the fastest kernel measured for (precision, p);
- * the others force one and return LHF_ERR_UNSUPPORTED where it has no instantiation. */
+ * the others force one and return LHF_ERR_UNSUPPORTED where it has no instantiation.  From p = 7 on,
+ * where the dense box maps allow (depth <= 8) and LHF_DETERMINISTIC is not asked, AUTO runs the M2L by
+ * quarter turns (every order, all levels in one launch; LDS atomics, so lhf_stats.deterministic is 0) in
+ * place of the kernel it would otherwise take; lhf_stats.m2l_kernel keeps that kernel's name. */
 #define LHF_M2L_AUTO 0
 #define LHF_M2L_HALF 1         /* batched VALU, each coefficient vector split over two lanes by the
                                   parity of m: p = 8, 10, 12, 16 (FP64 also 20, 22, 23, 24) */

@@ -28,19 +28,19 @@ namespace lhf {
 void m2l_tile_launch(const lhf_plan *Pl, int level, hipStream_t st);
 void m2l_mfma_launch(const lhf_plan *Pl, int level, hipStream_t st);
 void m2l_half_launch(const lhf_plan *Pl, int level, hipStream_t st);
+void turn_stage(const lhf_plan *Pl, bool scalar, hipStream_t st);
+void m2l_turn_launch(const lhf_plan *Pl, bool scalar, int only, hipStream_t st);
 void m2l_half_stage(const lhf_plan *Pl, int level, hipStream_t st);
 void m2l_quarter_launch(const lhf_plan *Pl, int level, hipStream_t st);
 bool m2l_half_scalar_supported(int precision, int p);
 void m2l_half_scalar_stage(const lhf_plan *Pl, int level, hipStream_t st);
 void m2l_half_scalar_launch(const lhf_plan *Pl, int level, hipStream_t st);
 void m2l_quarter_stage(const lhf_plan *Pl, int level, hipStream_t st);
-int m2l_quarter_max_ns(int p);
-int m2l_qmfma_max_ns(int p);
 void m2l_qmfma_launch(const lhf_plan *Pl, int level, hipStream_t st);
 void m2m_half_launch(const lhf_plan *Pl, int level, hipStream_t st);
-void l2l_half_launch(const lhf_plan *Pl, int level, hipStream_t st);
+void l2l_half_launch(const lhf_plan *Pl, int l, bool add, hipStream_t st);
 void m2m_quarter_launch(const lhf_plan *Pl, int level, hipStream_t st);
-void l2l_quarter_launch(const lhf_plan *Pl, int level, hipStream_t st);
+void l2l_quarter_launch(const lhf_plan *Pl, int l, bool add, hipStream_t st);
 
 constexpr int WAVE = 64;
 constexpr int NRMAX = (2 * MAXP * MAXP + WAVE - 1) / WAVE;  // accumulator rows per lane
@@ -484,7 +484,7 @@ __global__ void __launch_bounds__(WAVE) k_m2m(int p, int64_t off, const int32_t 
 
 // Downward pass for one level: L2L from the parent (levels > 2) + M2L over the V-list
 template <typename T>
-__global__ void __launch_bounds__(WAVE) k_down(int p, int level, int do_m2l, int64_t off, const int32_t *__restrict__ bparent,
+__global__ void __launch_bounds__(WAVE) k_down(int p, int level, int do_m2l, int add, int64_t off, const int32_t *__restrict__ bparent,
                                                const uint64_t *__restrict__ bkey, const int32_t *__restrict__ vcount,
                                                const int32_t *__restrict__ vsrc, const int16_t *__restrict__ vdir,
                                                const T *__restrict__ M, T *__restrict__ Lc, const T *__restrict__ rot,
@@ -530,7 +530,7 @@ __global__ void __launch_bounds__(WAVE) k_down(int p, int level, int do_m2l, int
     for (int k = 0; k < NRMAX; k++) {
         const int r = lane + WAVE * k;
         if (r >= 2 * P2) break;
-        out[r] = acc[k];
+        out[r] = add ? out[r] + acc[k] : acc[k];
     }
 }
 
@@ -1777,6 +1777,25 @@ static void translations(lhf_plan *P, hipStream_t st, bool scalar, const std::fu
                                P->bchild0, P->bnchild, P->bkey, M, rot, zph, P->dir_theta);
     }
     mark(3);
+    if (P->use_turn) {
+        // the M2L of every level in one launch, then L2L down the levels adds the parents' expansions
+        turn_stage(P, scalar, st);
+        mark(7 + 2 * 2);
+        m2l_turn_launch(P, scalar, -1, st);
+        mark(8 + 2 * 2);
+        for (int l = 3; l <= d; l++) {
+            mark(7 + 2 * l);
+            mark(8 + 2 * l);
+            if (P->lev[l].nb == 0) continue;
+            if (P->use_mmhalf) l2l_half_launch(P, l, true, st);
+            else if (P->use_mmquarter) l2l_quarter_launch(P, l, true, st);
+            else
+                hipLaunchKernelGGL(k_down<T>, dim3((unsigned)P->lev[l].nb), dim3(WAVE), sh_rcr, st, p, l, 0, 1,
+                                   P->lev[l].off, P->bparent, P->bkey, P->vcount, P->vsrc, P->vdir, (const T *)M,
+                                   Lc, rot, zph, P->dir_theta, coax);
+        }
+        return;
+    }
     for (int l = 2; l <= d; l++) {
         if (P->lev[l].nb == 0) {
             mark(7 + 2 * l);
@@ -1785,10 +1804,10 @@ static void translations(lhf_plan *P, hipStream_t st, bool scalar, const std::fu
         }
         if (P->use_tile) {
             // L2L from the parents (zeros at level 2), then the batched M2L adds into it
-            if (P->use_mmhalf) l2l_half_launch(P, l, st);
-            else if (P->use_mmquarter) l2l_quarter_launch(P, l, st);
+            if (P->use_mmhalf) l2l_half_launch(P, l, false, st);
+            else if (P->use_mmquarter) l2l_quarter_launch(P, l, false, st);
             else
-                hipLaunchKernelGGL(k_down<T>, dim3((unsigned)P->lev[l].nb), dim3(WAVE), sh_rcr, st, p, l, 0,
+                hipLaunchKernelGGL(k_down<T>, dim3((unsigned)P->lev[l].nb), dim3(WAVE), sh_rcr, st, p, l, 0, 0,
                                    P->lev[l].off, P->bparent, P->bkey, P->vcount, P->vsrc, P->vdir, (const T *)M,
                                    Lc, rot, zph, P->dir_theta, coax);
             // the half-vector kernel reads its sources from a copy in its lane layout
@@ -1806,7 +1825,7 @@ static void translations(lhf_plan *P, hipStream_t st, bool scalar, const std::fu
             mark(8 + 2 * l);
         } else {
             mark(7 + 2 * l);
-            hipLaunchKernelGGL(k_down<T>, dim3((unsigned)P->lev[l].nb), dim3(WAVE), sh_rcr, st, p, l, 1,
+            hipLaunchKernelGGL(k_down<T>, dim3((unsigned)P->lev[l].nb), dim3(WAVE), sh_rcr, st, p, l, 1, 0,
                                P->lev[l].off, P->bparent, P->bkey, P->vcount, P->vsrc, P->vdir, (const T *)M, Lc,
                                rot, zph, P->dir_theta, coax);
             mark(8 + 2 * l);
@@ -2046,17 +2065,19 @@ static lhf_status autotune_t(lhf_plan *P, const T *omega, int *ns, int *ts, hipS
         return ms;
     };
     for (int l = 0; l <= MAXDEPTH; l++) ns[l] = 0;
-    const int maxns = P->use_quarter ? m2l_quarter_max_ns(P->p) : P->use_qmfma ? m2l_qmfma_max_ns(P->p) : 0;
+    const int maxns = m2l_tile_range(P);
+    if (P->use_turn) turn_stage(P, false, st);
     for (int l = 2; l <= P->depth && maxns > 0 && rs == LHF_OK; l++) {
         if (P->lev[l].nb == 0) continue;
-        m2l_quarter_stage(P, l, st);
+        if (!P->use_turn) m2l_quarter_stage(P, l, st);
         int best = 0;
         float tbest = 0;
         for (int c : {1, 2, 3, 4, 6, 8, 10, 12, 16}) {
             if (c > maxns) break;
             P->m2l_ns[l] = c;
             const float t = timed([&] {
-                if (P->use_qmfma) m2l_qmfma_launch(P, l, st);
+                if (P->use_turn) m2l_turn_launch(P, false, l, st);
+                else if (P->use_qmfma) m2l_qmfma_launch(P, l, st);
                 else m2l_quarter_launch(P, l, st);
             });
             if (t >= 0 && (best == 0 || t < tbest)) {

@@ -155,6 +155,9 @@ struct lhf_plan {
     int m2l_ns[lhf::MAXDEPTH + 1] = {};  // targets per tile of the quarter-vector M2L per level (0: built-in)
     int p2p_ts = 0;                      // sources per LDS tile of the adaptive near field (0: built-in)
     void *wmm = nullptr, *wll = nullptr; // their rotation tables (S basis, R basis)
+    bool use_turn = false;               // batched M2L by quarter turns (any p it is built for)
+    bool turn_rows = false;              // with each vector split over a wavefront's rows (high p)
+    void *ttab = nullptr, *tscale = nullptr, *ttrig = nullptr, *tdir = nullptr;  // its tables
     bool tile2 = false;                  // VALU tile with two schedule rows per batch (FP32 p = 8, 10)
     void *wmfma = nullptr;               // per-class rotation blocks in MFMA A-operand lane order
 
@@ -180,6 +183,7 @@ lhf_status arg_error(const std::string &msg);
 lhf_status plan_new(lhf_plan **out, const lhf_desc *d, int nsys, const int64_t *off, const void *x,
                     const double *lo, const double *len, const double *a, hipStream_t stream);
 void plan_free(lhf_plan *P);
+int m2l_tile_range(const lhf_plan *P);
 
 // Device memory of plans and their temporaries.  Freed blocks are kept per (device, rounded
 // size) and handed to the next request of that size (a plan rebuilt every step allocates the

@@ -845,7 +845,7 @@ __global__ void __launch_bounds__(256, (hv::min_waves<T, P>())) k_mm_half(int64_
                                                                         T *__restrict__ dst_exp,
                                                                         const T *__restrict__ wtab, int64_t wstride,
                                                                         const int16_t *__restrict__ dir_theta,
-                                                                        const T *__restrict__ zph)
+                                                                        const T *__restrict__ zph, int add)
 {
     static_assert(KIND == 0 || KIND == 2, "M2M or L2L");
     using Sh = hv::Shape<T, P>;
@@ -1028,7 +1028,10 @@ __global__ void __launch_bounds__(256, (hv::min_waves<T, P>())) k_mm_half(int64_
 #pragma unroll
                 for (int jj = 0; jj < S(n); jj++) {
                     const int m = 2 * jj + hh;
-                    if (m <= n && !(pp && m == 0)) dp[n * n + pp * n + m] = v[hoff(n) + jj];
+                    if (m <= n && !(pp && m == 0)) {
+                        T *q2 = dp + n * n + pp * n + m;
+                        *q2 = add ? *q2 + v[hoff(n) + jj] : v[hoff(n) + jj];
+                    }
                 }
         }
     }
@@ -1122,7 +1125,7 @@ static bool mmhalf_build_t(lhf_plan *Pl, hipStream_t st)
 
 // KIND 0: M2M into the parents of level l; KIND 2: L2L from level l - 1 into level l (l >= 3)
 template <typename T, int P, int KIND>
-static void launch_mm(const lhf_plan *Pl, int l, hipStream_t st)
+static void launch_mm(const lhf_plan *Pl, int l, int add, hipStream_t st)
 {
     const int lp = KIND == 0 ? l : l - 1;
     const int64_t poff = Pl->lev[lp].off, npar = Pl->lev[lp].nb;
@@ -1132,7 +1135,7 @@ static void launch_mm(const lhf_plan *Pl, int l, hipStream_t st)
     T *dst = (T *)(KIND == 0 ? Pl->M : Pl->Lc);
     k_mm_half<T, P, KIND><<<dim3(grid), dim3(256), hv::mm_bytes<T, P>(), st>>>(
         poff, npar, Pl->bchild0, Pl->bnchild, Pl->bkey, src, dst, (const T *)(KIND == 0 ? Pl->wmm : Pl->wll),
-        8 * (int64_t)hv::Shape<T, P>::WHS, Pl->dir_theta, (const T *)Pl->zph);
+        8 * (int64_t)hv::Shape<T, P>::WHS, Pl->dir_theta, (const T *)Pl->zph, add);
 }
 
 template <typename T>
@@ -1167,37 +1170,37 @@ bool mmhalf_build(lhf_plan *Pl, hipStream_t st)
 }
 
 template <int KIND>
-static void mm_dispatch(const lhf_plan *Pl, int l, hipStream_t st)
+static void mm_dispatch(const lhf_plan *Pl, int l, int add, hipStream_t st)
 {
     if (Pl->precision == LHF_FP64) {
         switch (Pl->p) {
-        case 8: launch_mm<double, 8, KIND>(Pl, l, st); break;
-        case 10: launch_mm<double, 10, KIND>(Pl, l, st); break;
-        case 12: launch_mm<double, 12, KIND>(Pl, l, st); break;
-        case 16: launch_mm<double, 16, KIND>(Pl, l, st); break;
+        case 8: launch_mm<double, 8, KIND>(Pl, l, add, st); break;
+        case 10: launch_mm<double, 10, KIND>(Pl, l, add, st); break;
+        case 12: launch_mm<double, 12, KIND>(Pl, l, add, st); break;
+        case 16: launch_mm<double, 16, KIND>(Pl, l, add, st); break;
         }
     } else {
         switch (Pl->p) {
-        case 8: launch_mm<float, 8, KIND>(Pl, l, st); break;
-        case 10: launch_mm<float, 10, KIND>(Pl, l, st); break;
-        case 12: launch_mm<float, 12, KIND>(Pl, l, st); break;
-        case 16: launch_mm<float, 16, KIND>(Pl, l, st); break;
+        case 8: launch_mm<float, 8, KIND>(Pl, l, add, st); break;
+        case 10: launch_mm<float, 10, KIND>(Pl, l, add, st); break;
+        case 12: launch_mm<float, 12, KIND>(Pl, l, add, st); break;
+        case 16: launch_mm<float, 16, KIND>(Pl, l, add, st); break;
         }
     }
 }
 
 // M2M into the boxes of level l from their children
-void m2m_half_launch(const lhf_plan *Pl, int l, hipStream_t st) { mm_dispatch<0>(Pl, l, st); }
+void m2m_half_launch(const lhf_plan *Pl, int l, hipStream_t st) { mm_dispatch<0>(Pl, l, 0, st); }
 
-// L2L into the boxes of level l from their parents; level 2 starts from zero
-void l2l_half_launch(const lhf_plan *Pl, int l, hipStream_t st)
+// L2L into the boxes of level l from their parents (level 2 starts from zero); add: onto what they hold
+void l2l_half_launch(const lhf_plan *Pl, int l, bool add, hipStream_t st)
 {
     if (l <= 2) {
         if (Pl->precision == LHF_FP64) zero_level<double>(Pl, l, st);
         else zero_level<float>(Pl, l, st);
         return;
     }
-    mm_dispatch<2>(Pl, l, st);
+    mm_dispatch<2>(Pl, l, add, st);
 }
 
 // scalar harmonic FMM (phi only): the orders without half tiles

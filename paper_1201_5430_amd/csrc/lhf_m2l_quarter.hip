@@ -1058,7 +1058,7 @@ __global__ void __launch_bounds__(256, 1) k_mm_quarter(int64_t poff, int64_t npa
                                                     const double *__restrict__ src_exp, double *__restrict__ dst_exp,
                                                     const double *__restrict__ wq, int64_t wstride,
                                                     const int16_t *__restrict__ dir_theta,
-                                                    const double *__restrict__ zph)
+                                                    const double *__restrict__ zph, int add)
 {
     static_assert(KIND == 0 || KIND == 2, "M2M or L2L");
     using Sh = qv::Shape<P>;
@@ -1307,7 +1307,10 @@ __global__ void __launch_bounds__(256, 1) k_mm_quarter(int64_t poff, int64_t npa
 #pragma unroll
                     for (int jj = 0; jj < S(n); jj++) {
                         const int m = 4 * jj + q;
-                        if (m <= n && !(part && m == 0)) dp[n * n + part * n + m] = v[hoff(n) + jj];
+                        if (m <= n && !(part && m == 0)) {
+                            double *q2 = dp + n * n + part * n + m;
+                            *q2 = add ? *q2 + v[hoff(n) + jj] : v[hoff(n) + jj];
+                        }
                     }
             }
         }
@@ -1475,7 +1478,7 @@ static bool mmquarter_build_t(lhf_plan *Pl, hipStream_t st)
 
 // KIND 0: M2M into the parents of level l; KIND 2: L2L from level l - 1 into level l (l >= 3)
 template <int P, int KIND>
-static void launch_mm_quarter(const lhf_plan *Pl, int l, hipStream_t st)
+static void launch_mm_quarter(const lhf_plan *Pl, int l, int add, hipStream_t st)
 {
     // M2M: the parents of level l; L2L: the children of level l
     const int64_t off = Pl->lev[l].off, nb = Pl->lev[l].nb;
@@ -1487,7 +1490,7 @@ static void launch_mm_quarter(const lhf_plan *Pl, int l, hipStream_t st)
     k_mm_quarter<P, KIND><<<dim3(grid), dim3(256), 0, st>>>(
         off, nb, Pl->bchild0, Pl->bnchild, Pl->bparent, Pl->bkey, src, dst,
         (const double *)(KIND == 0 ? Pl->wmm : Pl->wll),
-        8 * (int64_t)qv::Shape<P>::WQS, Pl->dir_theta, (const double *)Pl->zph);
+        8 * (int64_t)qv::Shape<P>::WQS, Pl->dir_theta, (const double *)Pl->zph, add);
 }
 
 __global__ void k_zero_exp_q(int64_t count, double *__restrict__ dst)
@@ -1497,13 +1500,13 @@ __global__ void k_zero_exp_q(int64_t count, double *__restrict__ dst)
 }
 
 template <int KIND>
-static void mm_quarter_dispatch(const lhf_plan *Pl, int l, hipStream_t st)
+static void mm_quarter_dispatch(const lhf_plan *Pl, int l, int add, hipStream_t st)
 {
     switch (Pl->p) {
-    case 20: launch_mm_quarter<20, KIND>(Pl, l, st); break;
-    case 22: launch_mm_quarter<22, KIND>(Pl, l, st); break;
-    case 23: launch_mm_quarter<23, KIND>(Pl, l, st); break;
-    case 24: launch_mm_quarter<24, KIND>(Pl, l, st); break;
+    case 20: launch_mm_quarter<20, KIND>(Pl, l, add, st); break;
+    case 22: launch_mm_quarter<22, KIND>(Pl, l, add, st); break;
+    case 23: launch_mm_quarter<23, KIND>(Pl, l, add, st); break;
+    case 24: launch_mm_quarter<24, KIND>(Pl, l, add, st); break;
     }
 }
 
@@ -1628,10 +1631,10 @@ bool mmquarter_build(lhf_plan *Pl, hipStream_t st)
 }
 
 // M2M into the boxes of level l from their children
-void m2m_quarter_launch(const lhf_plan *Pl, int l, hipStream_t st) { mm_quarter_dispatch<0>(Pl, l, st); }
+void m2m_quarter_launch(const lhf_plan *Pl, int l, hipStream_t st) { mm_quarter_dispatch<0>(Pl, l, 0, st); }
 
 // L2L into the boxes of level l from their parents; level 2 starts from zero
-void l2l_quarter_launch(const lhf_plan *Pl, int l, hipStream_t st)
+void l2l_quarter_launch(const lhf_plan *Pl, int l, bool add, hipStream_t st)
 {
     if (l <= 2) {
         const int64_t cnt = Pl->lev[l].nb * 2 * (int64_t)Pl->p * Pl->p;
@@ -1640,7 +1643,7 @@ void l2l_quarter_launch(const lhf_plan *Pl, int l, hipStream_t st)
                 cnt, (double *)Pl->Lc + Pl->lev[l].off * 2 * (int64_t)Pl->p * Pl->p);
         return;
     }
-    mm_quarter_dispatch<2>(Pl, l, st);
+    mm_quarter_dispatch<2>(Pl, l, add, st);
 }
 
 }  // namespace lhf

@@ -36,6 +36,9 @@ bool m2l_mfma_supported(int precision, int p);
 bool m2l_half_supported(int precision, int p);
 bool whalf_build(lhf_plan *Pl, hipStream_t st);
 bool mmhalf_build(lhf_plan *Pl, hipStream_t st);
+int turn_kind(int precision, int p);
+bool turn_build(lhf_plan *Pl, hipStream_t st);
+size_t turn_src_values(const lhf_plan *Pl);
 bool wmfma_build(lhf_plan *Pl, hipStream_t st);
 
 bool m2l_tile_owned(int precision, int p);
@@ -110,6 +113,7 @@ struct Arena {
     char *base = nullptr;
     size_t cap = 0, off = 0;
     size_t need = 0;       // bytes the plan asked for when the arena ran out (0: it did not)
+    bool lean = false;     // second try: the M2L that needs no copy of the sources and no box maps
 };
 thread_local Arena *t_arena = nullptr;
 }  // namespace
@@ -1052,6 +1056,11 @@ static lhf_status build_tables(lhf_plan *P, hipStream_t st)
             set_error("matrix-core M2L set-up failed");
             return LHF_ERR_HIP;
         }
+        if (P->use_turn && !turn_build(P, st)) {
+            set_error("quarter-turn M2L set-up failed");
+            return LHF_ERR_HIP;
+        }
+        if (P->use_turn) return LHF_OK;
         P->use_half = P->m2l_kind == LHF_M2L_HALF;
         if (P->use_half && !whalf_build(P, st)) {
             set_error("half-vector M2L set-up failed");
@@ -1097,7 +1106,7 @@ static void free_plan(lhf_plan *P)
     for (int l = 0; l <= MAXDEPTH; l++)
         if (P->dmap[l]) (void)dev_free(P->dmap[l]);
     void *sb[] = {P->sched_cls_start, P->sched_c, P->sched_dir, P->sched_cls_theta, P->wpad, P->sched_row_start,
-                  P->sched_rows, P->wmfma, P->whalf, P->mh, P->dtab, P->wmm, P->wll, P->qsched};
+                  P->sched_rows, P->ttab, P->tscale, P->ttrig, P->tdir, P->wmfma, P->whalf, P->mh, P->dtab, P->wmm, P->wll, P->qsched};
     for (void *b : sb)
         if (b) (void)dev_free(b);
     delete P;
@@ -1268,7 +1277,7 @@ static lhf_status plan_create_t(lhf_plan *P, const void *x, hipStream_t st)
     CK(dev_malloc(&P->vcount, sizeof(int32_t) * tot));
     // batched M2L: used when a batched kernel exists for (precision, p) and the dense box maps
     // stay small (levels <= 8, at most 2^28 cells); then the V-lists are only counted
-    P->use_tile = P->m2l_kind != LHF_M2L_GENERIC;
+    P->use_tile = P->m2l_kind != LHF_M2L_GENERIC || P->use_turn;
     if (!P->use_tile) {
         CK(dev_malloc(&P->vsrc, sizeof(int32_t) * tot * VMAX));
         CK(dev_malloc(&P->vdir, sizeof(int16_t) * tot * VMAX));
@@ -1276,7 +1285,9 @@ static lhf_status plan_create_t(lhf_plan *P, const void *x, hipStream_t st)
     CK(dev_malloc(&P->M, sizeof(T) * tot * 2 * P2));
     CK(dev_malloc(&P->Lc, sizeof(T) * tot * 2 * P2));
     // L2P velocity coefficients, per leaf [3][p(p+1)/2] complex
-    CK(dev_malloc(&P->l2pv, sizeof(T) * (size_t)std::max<int64_t>(P->nleaf, 1) * 3 * P->p * (P->p + 1)));
+    // (the sources of the quarter-turn M2L use the same buffer before)
+    CK(dev_malloc(&P->l2pv, sizeof(T) * std::max((size_t)std::max<int64_t>(P->nleaf, 1) * 3 * P->p * (P->p + 1),
+                                                 P->use_turn ? turn_src_values(P) : (size_t)0)));
     // multipoles of levels 0 and 1 are never formed, yet kernels read box 0 as a stand-in
     // source for inactive lanes: every multipole starts as a defined zero
     CK(hipMemsetAsync(P->M, 0, sizeof(T) * tot * 2 * P2, st));
@@ -1563,8 +1574,9 @@ lhf_status plan_new(lhf_plan **out, const lhf_desc *d, int nsys, const int64_t *
     const bool adaptive_tree = d->max_per_leaf > 0;
     if (p == 0) tol_unmet = !choose_order(adaptive_tree, d->precision, d->tol, &p);
     int m2l_kind = 0, mm_kind = 0;
+    bool turn_dmap;
     {
-        const bool dmap_ok = d->depth <= 8 && ((int64_t)nsys << (3 * d->depth)) <= ((int64_t)1 << 28);
+        const bool dmap_ok = turn_dmap = d->depth <= 8 && ((int64_t)nsys << (3 * d->depth)) <= ((int64_t)1 << 28);
         lhf_status ks = resolve_kernels(d, p, dmap_ok, &m2l_kind, &mm_kind);
         if (ks != LHF_OK) return ks;
     }
@@ -1575,7 +1587,10 @@ lhf_status plan_new(lhf_plan **out, const lhf_desc *d, int nsys, const int64_t *
     P->p = p;
     P->m2l_kind = m2l_kind;
     P->mm_kind = mm_kind;
-    P->deterministic = kernel_deterministic(d->precision, p, m2l_kind);
+    P->use_turn = !(t_arena && t_arena->lean) && d->m2l_kernel == LHF_M2L_AUTO && !(d->flags & LHF_DETERMINISTIC) && turn_dmap &&
+                  turn_kind(d->precision, p) != 0;
+    P->turn_rows = turn_kind(d->precision, p) == 2;
+    P->deterministic = !P->use_turn && kernel_deterministic(d->precision, p, m2l_kind);
     P->p_from_tol = d->p == 0;
     P->out_grad = (d->flags & LHF_OUT_GRAD) != 0;
     calib_error(adaptive_tree, p, &P->calib_err_v, &P->calib_err_s);
@@ -1613,6 +1628,14 @@ lhf_status plan_new(lhf_plan **out, const lhf_desc *d, int nsys, const int64_t *
 }
 
 void plan_free(lhf_plan *P) { free_plan(P); }
+
+// targets per M2L tile that a caller may ask for (0: the plan's kernel has one shape)
+int m2l_tile_range(const lhf_plan *P)
+{
+    return P->m2l_kind == LHF_M2L_QUARTER ? m2l_quarter_max_ns(P->p)
+           : P->m2l_kind == LHF_M2L_QMFMA ? m2l_qmfma_max_ns(P->p)
+                                          : 0;
+}
 
 // Device memory of lhf_evaluate_noalloc: one copy of this array per device, held until the
 // process ends.  Its name is a host-side stand-in in host code; kernels only ever receive the
@@ -1765,6 +1788,12 @@ lhf_status lhf_evaluate_noalloc(const lhf_desc *d, int64_t n, const void *x, con
     t_arena = &ar;
     lhf_plan *P = nullptr;
     st = lhf_plan_create(&P, d, n, x, a, stream);
+    if (st < 0 && ar.need) {
+        // at orders whose other M2L kernel works without box maps and source copies, that may fit
+        ar.off = ar.need = 0;
+        ar.lean = true;
+        st = lhf_plan_create(&P, d, n, x, a, stream);
+    }
     lhf_status e = LHF_OK, dd = LHF_OK;
     if (st >= 0) {
         e = lhf_execute(P, omega, v, s, nullptr, stream);
@@ -1911,7 +1940,7 @@ static bool read_shapes(const char *path, const std::string &key, lhf_shapes *ou
 
 static lhf_status check_shapes(const lhf_plan *P, const lhf_shapes *sh)
 {
-    const int maxns = P->use_quarter ? m2l_quarter_max_ns(P->p) : P->use_qmfma ? m2l_qmfma_max_ns(P->p) : 0;
+    const int maxns = m2l_tile_range(P);
     for (int l = 0; l < LHF_SHAPE_LEVELS; l++)
         if (sh->m2l_tile[l] < 0 || sh->m2l_tile[l] > std::max(maxns, 0) || (maxns == 0 && sh->m2l_tile[l] != 0))
             return arg_error("m2l_tile out of range for this plan's M2L kernel");
