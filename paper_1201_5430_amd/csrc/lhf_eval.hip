@@ -21,6 +21,7 @@
 #include <algorithm>
 #include <math.h>
 
+#include "lhf_core.h"
 #include "lhf_internal.h"
 
 namespace lhf {
@@ -1108,10 +1109,7 @@ __global__ void __launch_bounds__(WAVE) k_m2p(int p, const int32_t *__restrict__
 
 // ---------------------------------------------------------------------------
 // P2P near field + combination + un-permutation: one lane per sorted element.
-// f = K/r^3, g = f'/r with the Gaussian core of eq. vem1; for u = r^2/(2a^2)
-// below 0.02 the Taylor series
-//   f = sqrt(2/pi)/a^3 sum_k (-u)^k/(k!(2k+3)),  g = sqrt(2/pi)/a^5 sum_{k>=1} (-1)^k u^(k-1)/((k-1)!(2k+3))
-// replaces the closed form (which cancels there).
+// f = K/r^3, g = f'/r with the Gaussian core of eq. vem1 (lhf_core.h):
 //   v += f (w_i x r),  s += f (w_i x w_j) + g (w_j . r)(w_i x r)
 // ---------------------------------------------------------------------------
 template <typename T>
@@ -1141,27 +1139,14 @@ __device__ inline void kernel_fg(T r2, T a, int smooth, T &f, T &g)
         return;
     }
     const T ia3 = ia2 * ia;
-    if (u < (T)0.02) {
-        // the series of K / r^3 and of its derivative term in u (coefficients folded at compile time)
-        T fs = 0, gs = 0, term = 1, t2 = -1;
-#pragma unroll
-        for (int k = 0; k < 12; k++) {
-            fs += term * (T)(1.0 / (2 * k + 3));
-            term *= -u * (T)(1.0 / (k + 1));
-        }
-#pragma unroll
-        for (int k = 1; k < 13; k++) {
-            gs += t2 * (T)(1.0 / (2 * k + 3));
-            t2 *= -u * (T)(1.0 / k);
-        }
-        f = c * ia3 * fs;
-        g = c * ia3 * ia2 * gs;
+    if (u < (T)1) {
+        f = c * ia3 * core::sker(u);
+        g = c * ia3 * ia2 * core::dker(u);
     } else {
         const T ir = rsqrt(r2);
-        const T r = r2 * ir;
-        const T ex = exp(-u);
-        const T ria = r * ia;
-        const T K = erf(ria * (T)0.70710678118654752440) - c * ria * ex;
+        const T ria = r2 * ir * ia;
+        const T ex = core::expm(u);
+        const T K = (T)1 - ex * (core::erfcx(ria * (T)0.70710678118654752440) + c * ria);
         const T ir2 = ir * ir;
         f = K * ir2 * ir;
         g = c * ex * ia3 * ir2 - (T)3 * f * ir2;
@@ -1276,110 +1261,164 @@ __device__ __forceinline__ void p2p_pair_grad(const Rec<T> &q, T xj, T yj, T zj,
     }
 }
 
-// far field + near field -> outputs in input order
-template <typename T, bool GRAD>
-__device__ __forceinline__ void p2p_store(int64_t i, int64_t n, const int32_t *__restrict__ perm,
-                                          const CompSum<T> *acc, T *__restrict__ vout, T *__restrict__ sout,
-                                          T *__restrict__ gout, T *__restrict__ bout)
+// targets of the next chunk of a leaf with 'rem' targets left, c of them with floor(64 / c) lanes each (or
+// as many times that as the workgroup has wavefronts): all that are left, unless that idles over a
+// quarter of the lanes
+__device__ __forceinline__ int p2p_chunk(int rem)
 {
-    const int64_t o = perm[i];
-    vout[3 * o] = acc[0].value();
-    vout[3 * o + 1] = acc[1].value();
-    vout[3 * o + 2] = acc[2].value();
-    sout[3 * o] = acc[3].value();
-    sout[3 * o + 1] = acc[4].value();
-    sout[3 * o + 2] = acc[5].value();
-    if constexpr (GRAD) {
-        T b = 0;
-        for (int k = 0; k < 9; k++) {
-            const T gk = acc[6 + k].value();
-            if (gout) gout[9 * o + k] = gk;
-            b += gk * gk;
-        }
-        if (bout) bout[o] = b;  // beta = grad v : grad v
-    }
+    const int c = min(64, rem);
+    return (64 / c) * c >= 48 ? c : (c >= 32 ? 32 : 16);
 }
 
-// near-field sum of one target over the elements st .. st+ct-1 (self excluded), added box by
-// box into compensated accumulators: v, s and, with GRAD, grad v
-template <typename T, bool GRAD, bool Q>
-__device__ __forceinline__ void p2p_box(int i, int st, int ct, const T *__restrict__ xw, T xj, T yj, T zj, T wjx,
-                                        T wjy, T wjz, T a, int sm, CompSum<T> *acc)
+// The NT lanes' sums (G = NT / c lanes per target, lane t + k c the k-th of target t, part q of a lane in
+// red[q * NT + lane]) added in the order of k to the far field, thread (target, part), and written out
+template <typename T, bool GRAD, int NT>
+__device__ __forceinline__ void p2p_finish(int64_t i0, int c, int G, int64_t n, int what, T *red, const T *__restrict__ vfar,
+                                           const int32_t *__restrict__ perm, T *__restrict__ vout,
+                                           T *__restrict__ sout, T *__restrict__ gout, T *__restrict__ bout)
 {
-    if constexpr (GRAD) {
-        T b[15];
-        for (int k = 0; k < 15; k++) b[k] = 0;
-        for (int e = 0; e < ct; e++) {
-            const int k = st + e;
-            if (k == i) continue;
-            p2p_pair_grad<T, Q>(load_rec<Q>(xw, k), xj, yj, zj, wjx, wjy, wjz, a, sm, b);
-        }
-        for (int k = 0; k < 15; k++) acc[k].add(b[k]);
-    } else {
-        T v0 = 0, v1 = 0, v2 = 0, s0 = 0, s1 = 0, s2 = 0;
-        for (int e = 0; e < ct; e++) {
-            const int k = st + e;
-            if (k == i) continue;
-            p2p_pair<T, Q>(load_rec<Q>(xw, k), xj, yj, zj, wjx, wjy, wjz, a, sm, v0, v1, v2, s0, s1, s2);
-        }
-        acc[0].add(v0);
-        acc[1].add(v1);
-        acc[2].add(v2);
-        acc[3].add(s0);
-        acc[4].add(s1);
-        acc[5].add(s2);
-    }
-}
-
-// uniform tree: one lane per sorted element over the 27 adjacent leaves (sources read from L1/L2:
-// the 64 targets of a wavefront are a few leaves of one neighbourhood), then combination with the
-// far field and un-permutation.  At the few elements per leaf of the uniform workloads this is
-// faster than staging each leaf's sources through LDS (2^20 cube FP64: 2.0 against 2.95 ms).
-template <typename T, bool GRAD, bool Q>
-__global__ void __launch_bounds__(256) k_p2p(int64_t n, int depth, int64_t leaf_off, const int32_t *__restrict__ eleaf,
-                                             const int32_t *__restrict__ ulist, const uint64_t *__restrict__ bkey,
-                                             const int32_t *__restrict__ bstart, const int32_t *__restrict__ bcount,
-                                             const T *__restrict__ xs, const T *__restrict__ ws,
-                                             const T *__restrict__ xw, const double *__restrict__ sys_a, int what,
-                                             const T *__restrict__ vfar,
-                                             const int32_t *__restrict__ perm, T *__restrict__ vout,
-                                             T *__restrict__ sout, T *__restrict__ gout, T *__restrict__ bout)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    // core radius of the element's system (0: singular kernel)
-    const T a = (T)sys_a[bkey[eleaf[i]] >> (3 * depth)];
-    const int smooth = a > (T)0;
     constexpr int NA = GRAD ? 15 : 6;
-    CompSum<T> acc[NA];
-    const T xj = xs[i], yj = xs[n + i], zj = xs[2 * n + i];
-    const T wjx = ws[i], wjy = ws[n + i], wjz = ws[2 * n + i];
-    if (what & 1)
-        for (int k = 0; k < NA; k++) acc[k].add(vfar[(size_t)k * n + i]);
-    if (what & 2) {
-        const int lf = eleaf[i];
-        const int32_t *U = ulist + (size_t)(lf - leaf_off) * 27;
-        for (int q = 0; q < 27; q++) {
-            const int nb = U[q];
-            if (nb < 0) continue;
-            p2p_box<T, GRAD, Q>((int)i, bstart[nb], bcount[nb], xw, xj, yj, zj, wjx, wjy, wjz, a, smooth, acc);
+    const int tid = threadIdx.x;
+    __syncthreads();
+    // part q of target t is read from, and its total left in, columns of target t alone
+    for (int w = tid; w < c * NA; w += NT) {
+        const int q = w / c, t = w % c;
+        CompSum<T> tot;
+        if (what & 1) tot.add(vfar[(size_t)q * n + i0 + t]);
+        T *r = red + q * NT + t;
+        for (int k = 0; k < G; k++) tot.add(r[k * c]);
+        const T val = tot.value();
+        if constexpr (GRAD) {
+            r[0] = val;
+        } else {
+            const int64_t o = perm[i0 + t];
+            if (q < 3) vout[3 * o + q] = val;
+            else sout[3 * o + q - 3] = val;
         }
     }
-    p2p_store<T, GRAD>(i, n, perm, acc, vout, sout, gout, bout);
+    __syncthreads();
+    if constexpr (GRAD) {
+        if (tid < c) {
+            const int64_t o = perm[i0 + tid];
+            const T *r = red + tid;
+            T b = 0;
+            for (int k = 0; k < 3; k++) {
+                vout[3 * o + k] = r[k * NT];
+                sout[3 * o + k] = r[(3 + k) * NT];
+            }
+            for (int k = 0; k < 9; k++) {
+                const T gk = r[(6 + k) * NT];
+                if (gout) gout[9 * o + k] = gk;
+                b += gk * gk;
+            }
+            if (bout) bout[o] = b;  // beta = grad v : grad v
+        }
+        __syncthreads();
+    }
 }
 
-// adaptive tree: near field of one target leaf per 64-lane workgroup, then combination with the
+// uniform tree: near field of one target leaf per workgroup of NT lanes.  The leaf's sources (up to 27
+// adjacent leaves) are numbered through by a prefix sum; c targets at a time take G = NT / c lanes each,
+// lane k of a target the sources k, k + G, ..  So all lanes work whatever the leaf holds (a lane per
+// target left a wavefront's lanes waiting for the fullest of their boxes, and 4,096 targets filled 64
+// wavefronts of the chip: 276 us, now 19; 10,007 elements 520 us, now 66).  The source indices go
+// through LDS; the records are read from L1/L2, the same one by one lane of every target.  Sums of 16
+// pairs enter compensated accumulators; all orders are fixed.
+constexpr int P2P_IX = 1024;
+
+template <typename T, bool GRAD, bool Q, int NT>
+__global__ void __launch_bounds__(NT) k_p2p(int64_t n, int depth, int64_t leaf_off, int64_t nleaf,
+                                            const int32_t *__restrict__ ulist, const uint64_t *__restrict__ bkey,
+                                            const int32_t *__restrict__ bstart, const int32_t *__restrict__ bcount,
+                                            const T *__restrict__ xw, const double *__restrict__ sys_a, int what,
+                                            const T *__restrict__ vfar, const int32_t *__restrict__ perm,
+                                            T *__restrict__ vout, T *__restrict__ sout, T *__restrict__ gout,
+                                            T *__restrict__ bout)
+{
+    constexpr int NA = GRAD ? 15 : 6;
+    __shared__ int pre[33], first[32];  // sources before box q of the list, first element of box q
+    __shared__ int ix[P2P_IX];
+    __shared__ T red[NT * NA];
+    const int tid = threadIdx.x;
+    // consecutive leaves stay on one XCD (shared L2)
+    const int64_t per = (nleaf + 7) / 8;
+    const int64_t lp = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
+    if (lp >= nleaf) return;
+    const int lf = (int)(leaf_off + lp);
+    const int i0 = bstart[lf], cnt = bcount[lf];
+    // core radius of the leaf's system (0: singular kernel)
+    const T a = (T)sys_a[bkey[lf] >> (3 * depth)];
+    const int smooth = a > (T)0;
+    if (tid < 32) {
+        const int nb = tid < 27 ? ulist[(size_t)lp * 27 + tid] : -1;
+        const int ct = nb >= 0 ? bcount[nb] : 0;
+        first[tid] = nb >= 0 ? bstart[nb] : 0;
+        int sum = ct;
+        for (int d = 1; d < 32; d <<= 1) {
+            const int o = __shfl_up(sum, d, 32);
+            if (tid >= d) sum += o;
+        }
+        pre[tid] = sum - ct;
+        if (tid == 31) pre[32] = sum;
+    }
+    __syncthreads();
+    const int S = (what & 2) ? pre[32] : 0;
+    int c;
+    for (int tb = 0; tb < cnt; tb += c) {
+        c = p2p_chunk(cnt - tb);
+        const int G = NT / c, k = tid / c, t = tid - k * c;
+        const bool tact = k < G;
+        const int i = i0 + tb + t;
+        const Rec<T> me = load_rec<false>(xw, i);
+        CompSum<T> acc[NA];
+        for (int j0 = 0; j0 < S; j0 += P2P_IX) {
+            const int m = min(S - j0, P2P_IX);
+            if (j0 > 0 || tb > 0) __syncthreads();  // the previous indices have been read
+            if (tb == 0 || S > P2P_IX)              // one chunk of indices serves every chunk of targets
+                for (int j = tid; j < m; j += NT) {
+                    int lo = 0;
+                    for (int d = 16; d > 0; d >>= 1)
+                        if (pre[lo + d] <= j0 + j) lo += d;
+                    ix[j] = first[lo] + j0 + j - pre[lo];
+                }
+            __syncthreads();
+            if (!tact) continue;
+            for (int j = k; j < m;) {
+                T part[NA];
+#pragma unroll
+                for (int q = 0; q < NA; q++) part[q] = 0;
+                for (int u = 0; u < 16 && j < m; u++, j += G) {
+                    // a wavefront of 64 targets: one source at a time, its record by scalar loads
+                    const int e = c == 64 ? __builtin_amdgcn_readfirstlane(ix[j]) : ix[j];
+                    if (e == i) continue;
+                    const Rec<T> r = load_rec<Q>(xw, e);
+                    if constexpr (GRAD) p2p_pair_grad<T, Q>(r, me.x, me.y, me.z, me.wx, me.wy, me.wz, a, smooth, part);
+                    else
+                        p2p_pair<T, Q>(r, me.x, me.y, me.z, me.wx, me.wy, me.wz, a, smooth, part[0], part[1], part[2],
+                                       part[3], part[4], part[5]);
+                }
+#pragma unroll
+                for (int q = 0; q < NA; q++) acc[q].add(part[q]);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < NA; q++) red[q * NT + tid] = acc[q].value();
+        p2p_finish<T, GRAD, NT>(i0 + tb, c, G, n, what, red, vfar, perm, vout, sout, gout, bout);
+    }
+}
+
+// adaptive tree: near field of one target leaf per workgroup of NT lanes, then combination with the
 // far field and un-permutation.  The leaf's source list (U-list leaves with the smoothed kernel,
 // then W/X boxes with the singular one) is staged through LDS in tiles of P2P_TS element records,
-// walked by the whole wavefront in list order.  Each
-// target takes G = 64 / c lanes (c: targets in the chunk, at most 64), lane k of a target sums the
+// walked by the whole workgroup in list order.  Each
+// target takes G = NT / c lanes (c: targets in the chunk, at most 64), lane k of a target sums the
 // tile's records k, k + G, ..; the G partial sums of a target are added in lane order at the end,
 // so the result is deterministic.  Smoothed and singular sources never share a tile (uniform
 // branch in the kernel).  Per tile the lane's partial sums enter compensated accumulators.
 constexpr int P2P_TS = 128;
 
-template <typename T, bool GRAD, bool Q, int TS = P2P_TS>
-__global__ void __launch_bounds__(64) k_p2p_tile(int64_t n, const int32_t *__restrict__ leaves,
+template <typename T, bool GRAD, bool Q, int TS, int NT>
+__global__ void __launch_bounds__(NT) k_p2p_tile(int64_t n, const int32_t *__restrict__ leaves,
                                                  const int8_t *__restrict__ blev, const int32_t *__restrict__ nl_start,
                                                  const int32_t *__restrict__ nl_ent, const uint64_t *__restrict__ bkey, const int32_t *__restrict__ bstart,
                                                  const int32_t *__restrict__ bcount, const T *__restrict__ xw,
@@ -1391,7 +1430,7 @@ __global__ void __launch_bounds__(64) k_p2p_tile(int64_t n, const int32_t *__res
     constexpr int NA = GRAD ? 15 : 6;
     __shared__ T tr[7][TS];          // x y z wx wy wz q of the staged sources
     __shared__ int tix[TS];          // their sorted indices (self exclusion)
-    __shared__ T red[64 * NA];       // partial sums of the lanes
+    __shared__ T red[NT * NA];       // partial sums of the lanes
     const int lane = threadIdx.x;
     const int64_t lp = blockIdx.x;
     const int b = leaves[lp];
@@ -1400,12 +1439,13 @@ __global__ void __launch_bounds__(64) k_p2p_tile(int64_t n, const int32_t *__res
     const int smooth = a > (T)0;
     const int s0 = bstart[b], cnt = bcount[b];
     const int ea = nl_start[lp], eb = nl_start[lp + 1];
-    for (int tb = 0; tb < cnt; tb += 64) {
-        const int c = min(64, cnt - tb);
-        const int G = 64 / c;
-        const int t = lane / G, k = lane - t * G;
-        const bool tact = t < c;
-        const int i = s0 + tb + (tact ? t : 0);
+    int c;
+    for (int tb = 0; tb < cnt; tb += c) {
+        c = p2p_chunk(cnt - tb);
+        const int G = NT / c;
+        const int k = lane / c, t = lane - k * c;
+        const bool tact = k < G;
+        const int i = s0 + tb + t;
         const Rec<T> me = load_rec<false>(xw, i);
         CompSum<T> acc[NA];
         if (what & 2) {
@@ -1424,7 +1464,7 @@ __global__ void __launch_bounds__(64) k_p2p_tile(int64_t n, const int32_t *__res
                         }
                         const int st = bstart[src], ct = bcount[src];
                         const int m = min(ct - o, TS - fill);
-                        for (int u = lane; u < m; u += 64) {
+                        for (int u = lane; u < m; u += NT) {
                             const Rec<T> r = load_rec<Q>(xw, st + o + u);
                             tr[0][fill + u] = r.x;
                             tr[1][fill + u] = r.y;
@@ -1464,20 +1504,10 @@ __global__ void __launch_bounds__(64) k_p2p_tile(int64_t n, const int32_t *__res
                 }
             }
         }
-        // the G lanes of a target, added in lane order, then the far field
+        // the G lanes of a target added in the order of k, then the far field
 #pragma unroll
-        for (int q = 0; q < NA; q++) red[lane * NA + q] = acc[q].value();
-        __syncthreads();
-        if (lane < c) {
-            const int64_t ii = s0 + tb + lane;
-            CompSum<T> tot[NA];
-            if (what & 1)
-                for (int q = 0; q < NA; q++) tot[q].add(vfar[(size_t)q * n + ii]);
-            for (int kk = 0; kk < G; kk++)
-                for (int q = 0; q < NA; q++) tot[q].add(red[(lane * G + kk) * NA + q]);
-            p2p_store<T, GRAD>(ii, n, perm, tot, vout, sout, gout, bout);
-        }
-        __syncthreads();
+        for (int q = 0; q < NA; q++) red[q * NT + lane] = acc[q].value();
+        p2p_finish<T, GRAD, NT>(s0 + tb, c, G, n, what, red, vfar, perm, vout, sout, gout, bout);
     }
 }
 
@@ -1727,17 +1757,29 @@ __global__ void k_gather_w(int64_t n, const T *__restrict__ w, const T *__restri
     if (q) qs[i] = qo;
 }
 
-template <typename T, bool GRAD, bool Q>
-static void p2p_launch(lhf_plan *P, int what, T *v, T *s, T *g, T *b, unsigned nblk, int tpb, hipStream_t st)
+// Four wavefronts a leaf instead of one where the leaves are too few to fill the chip's 1024 SIMDs with
+// eight wavefronts each (near field of 4,096 elements 19 us with four, 49 with one; 65,537 at depth 4
+// 199, 298), and, as long as the leaves alone don't, where they hold eight elements and more: the fullest
+// leaves would end last (ring of 400,003, 16 a leaf: 4.5 ms, 10.1; of 100,003 with gradient: 1.6, 3.8;
+// 56,000 leaves of a batch, 68 each: 16.8 ms for the whole call, 20.8).  Else one: 2^20 elements in
+// 262,144 leaves of four 1.00 ms with one, 2.45 with four; ring of 4.2 million, 16 a leaf, 18.5, 20.8.
+constexpr int64_t P2P_FEW = 8192, P2P_MANY = 131072;
+
+static bool p2p_wide(const lhf_plan *P)
+{
+    return P->nleaf < P2P_FEW || (P->nleaf < P2P_MANY && P->n >= 8 * P->nleaf);
+}
+
+template <typename T, bool GRAD, bool Q, int NT>
+static void p2p_launch_t(lhf_plan *P, int what, T *v, T *s, T *g, T *b, hipStream_t st)
 {
     const int64_t n = P->n;
     const int d = P->depth;
     if (P->adaptive) {
-        if (P->nleaf == 0) return;
         // the source tile: the plan's tuned choice on the v, s path, else the built-in one
         const int ts = (!GRAD && !Q && P->p2p_ts > 0) ? P->p2p_ts : P2P_TS;
 #define LHF_P2P_TILE(TSV)                                                                                       \
-    hipLaunchKernelGGL((k_p2p_tile<T, GRAD, Q, TSV>), dim3((unsigned)P->nleaf), dim3(64), 0, st, n, P->leaves,     \
+    hipLaunchKernelGGL((k_p2p_tile<T, GRAD, Q, TSV, NT>), dim3((unsigned)P->nleaf), dim3(NT), 0, st, n, P->leaves, \
                        P->blev, P->nl_start, P->nl_ent, P->bkey, P->bstart, P->bcount, (const T *)P->xw,           \
                        P->sys_a, what, (const T *)P->vfar, P->perm, v, s, g, b)
         if constexpr (!GRAD && !Q) {
@@ -1749,10 +1791,19 @@ static void p2p_launch(lhf_plan *P, int what, T *v, T *s, T *g, T *b, unsigned n
         }
 #undef LHF_P2P_TILE
     } else {
-        hipLaunchKernelGGL((k_p2p<T, GRAD, Q>), dim3(nblk), dim3(tpb), 0, st, n, d, P->lev[d].off, P->eleaf,
-                           P->ulist, P->bkey, P->bstart, P->bcount, (const T *)P->xs, (const T *)P->ws,
-                           (const T *)P->xw, P->sys_a, what, (const T *)P->vfar, P->perm, v, s, g, b);
+        const int64_t nleaf = P->lev[d].nb;
+        hipLaunchKernelGGL((k_p2p<T, GRAD, Q, NT>), dim3((unsigned)((nleaf + 7) / 8 * 8)), dim3(NT), 0, st, n, d,
+                           P->lev[d].off, nleaf, P->ulist, P->bkey, P->bstart, P->bcount, (const T *)P->xw, P->sys_a,
+                           what, (const T *)P->vfar, P->perm, v, s, g, b);
     }
+}
+
+template <typename T, bool GRAD, bool Q>
+static void p2p_launch(lhf_plan *P, int what, T *v, T *s, T *g, T *b, hipStream_t st)
+{
+    if (P->nleaf == 0) return;
+    if (p2p_wide(P)) p2p_launch_t<T, GRAD, Q, 256>(P, what, v, s, g, b, st);
+    else p2p_launch_t<T, GRAD, Q, 64>(P, what, v, s, g, b, st);
 }
 
 // M2M into levels depth-1 .. 2, then per level L2L and M2L (events ev[3] after the upward pass and
@@ -1903,10 +1954,10 @@ static lhf_status execute_t(lhf_plan *P, const lhf_io *io, hipStream_t st)
     mark(5);
     const bool gr = grad_v || beta;
     T *vo = (T *)v, *so = (T *)s, *go = (T *)grad_v, *bo = (T *)beta;
-    if (gr && qin) p2p_launch<T, true, true>(P, what, vo, so, go, bo, nblk, tpb, st);
-    else if (gr) p2p_launch<T, true, false>(P, what, vo, so, go, bo, nblk, tpb, st);
-    else if (qin) p2p_launch<T, false, true>(P, what, vo, so, nullptr, nullptr, nblk, tpb, st);
-    else p2p_launch<T, false, false>(P, what, vo, so, nullptr, nullptr, nblk, tpb, st);
+    if (gr && qin) p2p_launch<T, true, true>(P, what, vo, so, go, bo, st);
+    else if (gr) p2p_launch<T, true, false>(P, what, vo, so, go, bo, st);
+    else if (qin) p2p_launch<T, false, true>(P, what, vo, so, nullptr, nullptr, st);
+    else p2p_launch<T, false, false>(P, what, vo, so, nullptr, nullptr, st);
     mark(6);
     LHF_HIP(hipGetLastError());
     return LHF_OK;
@@ -2093,7 +2144,7 @@ static lhf_status autotune_t(lhf_plan *P, const T *omega, int *ns, int *ts, hipS
         float tbest = 0;
         for (int c : {64, 128, 256}) {
             P->p2p_ts = c;
-            const float t = timed([&] { p2p_launch<T, false, false>(P, 2, v, s, nullptr, nullptr, 0, 0, st); });
+            const float t = timed([&] { p2p_launch<T, false, false>(P, 2, v, s, nullptr, nullptr, st); });
             if (t >= 0 && (best == 0 || t < tbest)) {
                 best = c;
                 tbest = t;
