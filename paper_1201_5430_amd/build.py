@@ -12,8 +12,9 @@ LIB = os.path.join(HERE, "liblhfmm.so")
 SOURCES = ["lhf_plan.hip", "lhf_eval.hip", "lhf_m2l.hip", "lhf_m2l_half.hip", "lhf_m2l_quarter.hip",
            "lhf_m2l_turn.hip", "lhf_m2l_mfma.hip", "lhf_batch.hip", "lhf_filament.hip"]
 # compiled once per type and order: whole vectors per lane, vectors split over a wavefront's rows
-TURN = [("turn", "double", p) for p in range(7, 13)] + [("turn", "float", p) for p in range(7, 17)] + \
-    [("rows", "double", p) for p in range(13, 25)]
+TURN = [("m2l_turn", "double", p) for p in range(7, 13)] + [("m2l_turn", "float", p) for p in range(7, 17)] + \
+    [("m2l_rows", "double", p) for p in range(13, 25)] + \
+    [("mm_rows", "double", p) for p in range(7, 25)] + [("mm_rows", "float", p) for p in range(7, 17)]
 ARCH = os.environ.get("LHF_OFFLOAD_ARCH", "gfx950")
 
 FLAGS = [
@@ -32,7 +33,7 @@ EXTRA = {"lhf_m2l_half.hip": ["-mllvm", "-pragma-unroll-threshold=200000"],
 
 def units():
     """(object, source, extra flags) of every compilation, the longest first"""
-    out = [(f"lhf_m2l_{k}_{t}_{p}.o", f"lhf_m2l_{k}_p.hip", [f"-DLHF_TURN_T={t}", f"-DLHF_TURN_P={p}"])
+    out = [(f"lhf_{k}_{t}_{p}.o", f"lhf_{k}_p.hip", [f"-DLHF_TURN_T={t}", f"-DLHF_TURN_P={p}"])
            for k, t, p in sorted(TURN, key=lambda u: -u[2])]
     rest = [(s.replace(".hip", ".o"), s, EXTRA.get(s, [])) for s in SOURCES]
     return sorted(rest, key=lambda u: u[1] not in EXTRA)[:len(EXTRA)] + out + \

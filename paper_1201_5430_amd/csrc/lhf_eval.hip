@@ -30,6 +30,7 @@ void m2l_tile_launch(const lhf_plan *Pl, int level, hipStream_t st);
 void m2l_mfma_launch(const lhf_plan *Pl, int level, hipStream_t st);
 void m2l_half_launch(const lhf_plan *Pl, int level, hipStream_t st);
 void turn_stage(const lhf_plan *Pl, bool scalar, hipStream_t st);
+void mm_rows(const lhf_plan *Pl, bool down, int l, hipStream_t st);
 void m2l_turn_launch(const lhf_plan *Pl, bool scalar, int only, hipStream_t st);
 void m2l_half_stage(const lhf_plan *Pl, int level, hipStream_t st);
 void m2l_quarter_launch(const lhf_plan *Pl, int level, hipStream_t st);
@@ -1821,7 +1822,8 @@ static void translations(lhf_plan *P, hipStream_t st, bool scalar, const std::fu
         size_t sh_rcr = sizeof(T) * (4 * P2 + 2 * ZS + 2 * p + 2);
     for (int l = d - 1; l >= 2; l--) {
         if (P->lev[l].nb == 0) continue;
-        if (P->use_mmhalf) m2m_half_launch(P, l, st);
+        if (P->use_mmrows) mm_rows(P, false, l, st);
+        else if (P->use_mmhalf) m2m_half_launch(P, l, st);
         else if (P->use_mmquarter) m2m_quarter_launch(P, l, st);
         else
             hipLaunchKernelGGL(k_m2m<T>, dim3((unsigned)P->lev[l].nb), dim3(WAVE), sh_rcr, st, p, P->lev[l].off,
@@ -1838,7 +1840,8 @@ static void translations(lhf_plan *P, hipStream_t st, bool scalar, const std::fu
             mark(7 + 2 * l);
             mark(8 + 2 * l);
             if (P->lev[l].nb == 0) continue;
-            if (P->use_mmhalf) l2l_half_launch(P, l, true, st);
+            if (P->use_mmrows) mm_rows(P, true, l, st);
+            else if (P->use_mmhalf) l2l_half_launch(P, l, true, st);
             else if (P->use_mmquarter) l2l_quarter_launch(P, l, true, st);
             else
                 hipLaunchKernelGGL(k_down<T>, dim3((unsigned)P->lev[l].nb), dim3(WAVE), sh_rcr, st, p, l, 0, 1,

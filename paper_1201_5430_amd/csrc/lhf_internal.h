@@ -157,6 +157,8 @@ struct lhf_plan {
     void *wmm = nullptr, *wll = nullptr; // their rotation tables (S basis, R basis)
     bool use_turn = false;               // batched M2L by quarter turns (any p it is built for)
     bool turn_rows = false;              // with each vector split over a wavefront's rows (high p)
+    bool use_mmrows = false;             // M2M and L2L by quarter turns (beside use_turn)
+    void *mmtab = nullptr;               // their tables
     void *ttab = nullptr, *tscale = nullptr, *ttrig = nullptr, *tdir = nullptr;  // its tables
     bool tile2 = false;                  // VALU tile with two schedule rows per batch (FP32 p = 8, 10)
     void *wmfma = nullptr;               // per-class rotation blocks in MFMA A-operand lane order

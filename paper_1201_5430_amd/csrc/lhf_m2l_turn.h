@@ -312,6 +312,37 @@ inline size_t fixed_bytes(int p, int npot)
 inline size_t slot_bytes(int p, int npot) { return sizeof(double) * acc_stride(p, npot) + VMAX * 6 + 8; }
 }  // namespace tr
 
+// M2M and L2L in the same split (lhf_mm_rows_p.hip)
+namespace tm {
+// column j of the shift: R = p - 2j orders: the triangle's diagonals, then a factor per order
+__host__ __device__ constexpr int hoff_tab(int p, int j)
+{
+    int o = 0;
+    for (int k = 0; k < j; k++) o += (p - 2 * k) * (p - 2 * k + 1) / 2 + (p - 2 * k);
+    return o;
+}
+template <typename T>
+__host__ __device__ constexpr int htab(int p) { return tn::pad(hoff_tab(p, (p + 1) / 2), tr::chunk<T>()); }
+// turns, shifts of M2M and of L2L, then the scales into and out of the orthonormal basis for each
+template <typename T>
+__host__ __device__ constexpr int tab_size(int p) { return 4 * tr::ytab<T>(p) + 4 * htab<T>(p) + 4 * p * p; }
+// entries of orders 2k, 2k + 1 (one potential), and the length of a stretch in LDS (odd)
+__host__ __device__ constexpr int count(int p, int k) { return 2 * k + 1 < p ? 8 * k + 4 : 4 * k + 1; }
+__host__ __device__ constexpr int stretch(int p) { return (8 * ((p + 1) / 2) - 4) | 1; }
+// wavefronts per SIMD
+template <typename T, int P>
+constexpr int waves()
+{
+    return sizeof(T) == 8 ? (P <= 16 ? 2 : 1) : 2;
+}
+template <typename T, int P>
+__host__ __device__ constexpr size_t bytes()
+{
+    return sizeof(T) * (4 * tr::ytab<T>(P) + 2 * htab<T>(P) + 32 * P + 2 * P * P +
+                        4 * (size_t)waves<T, P>() * 16 * stretch(P));
+}
+}  // namespace tm
+
 // one translation unit per (T, P): the kernels with both potentials and with the scalar one
 template <typename T, int P>
 hipError_t turn_attr();
@@ -321,5 +352,9 @@ template <typename T, int P>
 hipError_t rows_attr();
 template <typename T, int P>
 void rows_launch(const lhf_plan *Pl, bool scalar, int only, hipStream_t st);
+template <typename T, int P>
+hipError_t mm_rows_attr();
+template <typename T, int P>
+void mm_rows_launch(const lhf_plan *Pl, bool down, int l, bool add, hipStream_t st);
 
 }  // namespace lhf

@@ -107,6 +107,54 @@ __global__ void k_turn_tab(int p, bool rows, int size, T *__restrict__ tab, T *_
         scale[p * p + t] = (T)(sg * N / c);
     }
 }
+// entry t of the M2M and L2L tables (lhf_mm_rows_p.hip): the turns of rows_entry, [M2M, L2L][parity] shifts
+// of th entries, [M2M, L2L][into, out of the orthonormal basis] scales.  The distance of child and parent is
+// sqrt(3) / 4 of the parent's size, sqrt(3) / 2 of the child's; (-tau)^k / k! are the shift's coefficients
+// in the stored basis and 2^-n the ratio of the sizes.
+__device__ double mm_entry(int p, int ty, int th, int t)
+{
+    if (t < 4 * ty) return rows_entry(p, ty, 0, t);
+    t -= 4 * ty;
+    const double taup = 0.4330127018922193;
+    if (t >= 4 * th) {
+        t -= 4 * th;
+        const int kind = t / (2 * p * p), dir = t / (p * p) & 1, i = t % (p * p);
+        int n = (int)sqrtf((float)i);
+        while ((n + 1) * (n + 1) <= i) n++;
+        while (n * n > i) n--;
+        const int r = i - n * n, m = r > n ? r - n : r;
+        const double N = sqrt(fact(n - m)) * sqrt(fact(n + m)), c = m ? sqrt(2.0) : 1.0, sg = (m & 1) ? -1.0 : 1.0;
+        return kind == 0 ? (dir ? 1.0 / (c * N) : sg * c * N) : (dir ? sg * N / c : c / N);
+    }
+    const int kind = t / (2 * th), par = t / th & 1;
+    int o = t % th, j = 0;
+    for (; 2 * j < p; j++) {
+        const int R = p - 2 * j, sz = R * (R + 1) / 2 + R;
+        if (o < sz) break;
+        o -= sz;
+    }
+    if (2 * j >= p) return 0.0;
+    const int n0 = 2 * j, R = p - n0, m = n0 + par, q1 = R * (R + 1) / 2;
+    if (o < q1) {
+        const tr::Sym y = tr::sym(R, o);
+        const int lo = n0 + y.r, hi = n0 + y.c;
+        if (lo < m) return 0.0;
+        double cf = 1.0;
+        for (int k = 1; k <= hi - lo; k++) cf *= -taup / (double)k;
+        const double q = sqrt(fact(hi - m) / fact(lo - m)) * sqrt(fact(hi + m) / fact(lo + m));
+        return ((m & 1) ? -1.0 : 1.0) * ldexp(cf * q, -lo);
+    }
+    o -= q1;
+    const int n = kind == 0 ? n0 + R - 1 - o : n0 + o + 1;
+    if (n < 1 || n < m) return 0.0;
+    return (kind == 0 ? taup : -2.0 * taup) * sqrt((double)n * n - (double)m * m) / (double)n;
+}
+template <typename T>
+__global__ void k_mm_tab(int p, int size, T *__restrict__ tab)
+{
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < size) tab[t] = (T)mm_entry(p, tr::ytab<T>(p), tm::htab<T>(p), t);
+}
 
 // a direction of every row of the angle table (azimuths, then polar angles) and the rows of every
 // direction
@@ -243,6 +291,11 @@ bool build_t(lhf_plan *Pl, hipStream_t st)
     k_turn_tab<T><<<dim3((size + 255) / 256), dim3(256), 0, st>>>(p, Pl->turn_rows, size, (T *)Pl->ttab, (T *)Pl->tscale);
     static const Rows rows = make_rows();
     k_turn_trig<T><<<dim3(tn::NROW), dim3(64), 0, st>>>(p, rows, (T *)Pl->ttrig, (tn::Dir *)Pl->tdir);
+    if (Pl->use_mmrows) {
+        const int mm = tm::tab_size<T>(p);
+        if (dev_malloc(&Pl->mmtab, sizeof(T) * mm) != hipSuccess) return false;
+        k_mm_tab<T><<<dim3((mm + 63) / 64), dim3(64), 0, st>>>(p, mm, (T *)Pl->mmtab);
+    }
     return true;
 }
 
@@ -302,9 +355,9 @@ int turn_kind(int precision, int p)
 bool turn_build(lhf_plan *Pl, hipStream_t st)
 {
 #define F(N) \
-    if (Pl->p == N) return build_t<T>(Pl, st) && turn_attr<T, N>() == hipSuccess;
+    if (Pl->p == N) return build_t<T>(Pl, st) && turn_attr<T, N>() == hipSuccess && mm_rows_attr<T, N>() == hipSuccess;
 #define G(N) \
-    if (Pl->p == N) return build_t<T>(Pl, st) && rows_attr<T, N>() == hipSuccess;
+    if (Pl->p == N) return build_t<T>(Pl, st) && rows_attr<T, N>() == hipSuccess && mm_rows_attr<T, N>() == hipSuccess;
     if (Pl->precision == LHF_FP64) {
         using T = double;
         LHF_TURN_FP64(F) LHF_ROWS_FP64(G)
@@ -339,6 +392,21 @@ void m2l_turn_launch(const lhf_plan *Pl, bool scalar, int only, hipStream_t st)
     }
 #undef F
 #undef G
+}
+
+// M2M into the boxes of level l (down: L2L into them, added to what they hold)
+void mm_rows(const lhf_plan *Pl, bool down, int l, hipStream_t st)
+{
+#define F(N) \
+    if (Pl->p == N) return mm_rows_launch<T, N>(Pl, down, l, true, st);
+    if (Pl->precision == LHF_FP64) {
+        using T = double;
+        LHF_TURN_FP64(F) LHF_ROWS_FP64(F)
+    } else {
+        using T = float;
+        LHF_TURN_FP32(F)
+    }
+#undef F
 }
 
 }  // namespace lhf

@@ -1004,6 +1004,21 @@ static lhf_status build_tables(lhf_plan *P, hipStream_t st)
     P->n_theta = (int)theta.size();
     P->h_theta = theta;
     const int p = P->p;
+    if (P->use_turn) {
+        for (int l = 2; l <= P->depth; l++) {
+            const size_t cells = (size_t)P->nsys << (3 * l);
+            LHF_HIP(dev_malloc(&P->dmap[l], sizeof(int32_t) * cells));
+            LHF_HIP(hipMemsetAsync(P->dmap[l], 0xff, sizeof(int32_t) * cells, st));
+            dmap_build(P, l, st);
+        }
+        if (!turn_build(P, st)) {
+            set_error("quarter-turn M2L set-up failed");
+            return LHF_ERR_HIP;
+        }
+        // no translation reads the rotations of the polar-angle classes (10,007 elements at p = 12: 160 us
+        // of a one-shot evaluation)
+        if (P->use_mmrows) return LHF_OK;
+    }
     const size_t RS = rot_set_size(p);
     LHF_HIP(dev_malloc(&P->rot, sizeof(T) * RS * ROT_NKIND * theta.size()));
     LHF_HIP(dev_malloc(&P->zph, sizeof(T) * NDIR * 2 * p));
@@ -1020,18 +1035,18 @@ static lhf_status build_tables(lhf_plan *P, hipStream_t st)
     hipLaunchKernelGGL(k_coax<T>, dim3(1), dim3(32), 0, st, p, (T *)P->coax);
     LHF_HIP(hipGetLastError());
     // batched M2M and L2L: two lanes per part vector (p = 8-16) or four (FP64 p = 20-24)
-    P->use_mmhalf = P->mm_kind == LHF_MM_HALF;
+    P->use_mmhalf = !P->use_mmrows && P->mm_kind == LHF_MM_HALF;
     if (P->use_mmhalf && !mmhalf_build(P, st)) {
         set_error("batched M2M/L2L set-up failed");
         return LHF_ERR_HIP;
     }
-    P->use_mmquarter = P->mm_kind == LHF_MM_QUARTER;
+    P->use_mmquarter = !P->use_mmrows && P->mm_kind == LHF_MM_QUARTER;
     if (P->use_mmquarter && !mmquarter_build(P, st)) {
         set_error("quarter-vector M2M/L2L set-up failed");
         return LHF_ERR_HIP;
     }
     // batched M2L (decided with the tree): schedule, padded rotation blocks, dense box maps
-    if (P->use_tile) {
+    if (P->use_tile && !P->use_turn) {
         lhf_status s = build_schedule(P, cls, (int)theta.size(), st);
         if (s != LHF_OK) return s;
         const bool tile_ok = P->m2l_kind == LHF_M2L_TILE || P->m2l_kind == LHF_M2L_TILE1;
@@ -1056,11 +1071,6 @@ static lhf_status build_tables(lhf_plan *P, hipStream_t st)
             set_error("matrix-core M2L set-up failed");
             return LHF_ERR_HIP;
         }
-        if (P->use_turn && !turn_build(P, st)) {
-            set_error("quarter-turn M2L set-up failed");
-            return LHF_ERR_HIP;
-        }
-        if (P->use_turn) return LHF_OK;
         P->use_half = P->m2l_kind == LHF_M2L_HALF;
         if (P->use_half && !whalf_build(P, st)) {
             set_error("half-vector M2L set-up failed");
@@ -1106,7 +1116,7 @@ static void free_plan(lhf_plan *P)
     for (int l = 0; l <= MAXDEPTH; l++)
         if (P->dmap[l]) (void)dev_free(P->dmap[l]);
     void *sb[] = {P->sched_cls_start, P->sched_c, P->sched_dir, P->sched_cls_theta, P->wpad, P->sched_row_start,
-                  P->sched_rows, P->ttab, P->tscale, P->ttrig, P->tdir, P->wmfma, P->whalf, P->mh, P->dtab, P->wmm, P->wll, P->qsched};
+                  P->sched_rows, P->mmtab, P->ttab, P->tscale, P->ttrig, P->tdir, P->wmfma, P->whalf, P->mh, P->dtab, P->wmm, P->wll, P->qsched};
     for (void *b : sb)
         if (b) (void)dev_free(b);
     delete P;
@@ -1589,6 +1599,7 @@ lhf_status plan_new(lhf_plan **out, const lhf_desc *d, int nsys, const int64_t *
     P->mm_kind = mm_kind;
     P->use_turn = !(t_arena && t_arena->lean) && d->m2l_kernel == LHF_M2L_AUTO && !(d->flags & LHF_DETERMINISTIC) && turn_dmap &&
                   turn_kind(d->precision, p) != 0;
+    P->use_mmrows = P->use_turn && d->mm_kernel == LHF_MM_AUTO;
     P->turn_rows = turn_kind(d->precision, p) == 2;
     P->deterministic = !P->use_turn && kernel_deterministic(d->precision, p, m2l_kind);
     P->p_from_tol = d->p == 0;
