@@ -88,8 +88,12 @@ __device__ inline void box_centre(uint64_t key, int level, const double *__restr
 // (R_n^m = (-1)^n i^m Rt_n^m) by the recurrence
 //   Rt_m^m = -(x+iy)/(2m) Rt_{m-1}^{m-1},  Rt_{m+1}^m = z Rt_m^m,
 //   Rt_n^m = ((2n-1) z Rt_{n-1}^m - r^2 Rt_{n-2}^m) / ((n-m)(n+m)),
-// (the divisions by tables of reciprocals), then every thread adds the eq. eve4 contributions of
-// its (n, m) pair (both potentials, Re and Im).  The columns are stored as triangles (n, m <= n).
+// (the divisions by tables of reciprocals), then every thread adds its pair's products with the strengths
+// (two LDS reads and up to eight FMAs an element).  Eq. eve4 is linear in these sums, so it is applied
+// once per leaf, to the sums of the pairs around (n, m), instead of once per element (twelve LDS reads and
+// some sixty operations).  The columns are stored as triangles (n, m <= n).
+// P2M before and now: ring of 4.2 million, FP64 p = 23 14.1 -> 6.0 ms; 2^20 segments of filaments, p = 12 10.9
+// -> 4.0 ms; 2^20 elements, p = 12 1.5 -> 1.2 ms.  The harmonics' recurrences bound it now.
 // ---------------------------------------------------------------------------
 // SC: scalar harmonic FMM -- phi = sum q g_n^m (the expansion of eq. rsbf5 of each source), chi = 0.
 // SEG: vortex filaments -- each element is a segment (centre x, vector sl) expanded as nq
@@ -106,7 +110,7 @@ inline void p2m_config(int p, size_t tsize, int &nthr, int &ch, size_t &shm)
     nthr = std::min(P2M_MAXT, (TRI + WAVE - 1) / WAVE * WAVE);
     const size_t fixed = tsize * (size_t)(TRI + p + 1);
     const size_t per = tsize * (size_t)(2 * TRI + 4);
-    ch = (int)std::max<size_t>(1, std::min<size_t>(16, (40960 - fixed) / per));
+    ch = (int)std::max<size_t>(4, std::min<size_t>(16, (40960 - fixed) / per));  // 4: the sums of eight take its place
     shm = fixed + per * (size_t)ch;
 }
 
@@ -150,7 +154,7 @@ __global__ void __launch_bounds__(P2M_MAXT) k_p2m(int p, int depth, int64_t leaf
     int nn = 0;
     while (own && tri_idx(nn + 1, 0) <= tid) nn++;
     const int m = own ? tid - tri_idx(nn, 0) : 0;
-    T acc[4] = {0, 0, 0, 0};  // Re a, Im a, Re b, Im b
+    T acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};  // sums of omega_x, omega_y, omega_z, q times (Re, Im) Rt_n^m
     const int s0 = bstart[b], cnt = bcount[b] * (SEG ? nq : 1);  // SEG: (element, quadrature point)
     for (int e0 = 0; e0 < cnt; e0 += ch) {
         const int ne = min(ch, cnt - e0);
@@ -205,75 +209,86 @@ __global__ void __launch_bounds__(P2M_MAXT) k_p2m(int p, int depth, int64_t leaf
         }
         __syncthreads();
         if (!own) continue;
-        // the three conj(Rt) values of order n (phi) and of order n - 1 (chi) serve all four
-        // outputs (Re and Im of a and b)
-        const T sgn = (m & 1) ? (T)-1 : (T)1;
         for (int e = 0; e < ne; e++) {
-            const T *Re = Rre + (size_t)e * TRI, *Im = Rim + (size_t)e * TRI;
-            const T wx = wsh[4 * e], wy = wsh[4 * e + 1], wz = wsh[4 * e + 2], qe = wsh[4 * e + 3];
-            // conj(Rt_n^k), with the convention conj(Rt_n^{-1}) = -Rt_n^1 that makes the m >= 1
-            // formulas valid at m = 0 as well
-            auto C = [&](int n2, int kk, T &re, T &im) {
-                if (n2 < 0 || kk > n2) {
-                    re = 0;
-                    im = 0;
-                } else if (kk == -1) {
-                    if (n2 >= 1) {
-                        re = -Re[tri_idx(n2, 1)];
-                        im = -Im[tri_idx(n2, 1)];
-                    } else {
-                        re = 0;
-                        im = 0;
-                    }
-                } else {
-                    re = Re[tri_idx(n2, kk)];
-                    im = -Im[tri_idx(n2, kk)];
-                }
-            };
-            const T wmre = wx, wmim = -wy;  // wx - i wy
-            const T wpre = wx, wpim = wy;   // wx + i wy
-            if constexpr (SC) {
-                T c3re, c3im;
-                C(nn, m, c3re, c3im);
-                acc[0] += qe * sgn * c3re;
-                acc[1] += qe * sgn * c3im;
-                continue;
+            const T re = Rre[(size_t)e * TRI + tid], im = Rim[(size_t)e * TRI + tid];
+            if constexpr (!SC) {
+                const T wx = wsh[4 * e], wy = wsh[4 * e + 1], wz = wsh[4 * e + 2];
+                acc[0] += wx * re;
+                acc[1] += wx * im;
+                acc[2] += wy * re;
+                acc[3] += wy * im;
+                acc[4] += wz * re;
+                acc[5] += wz * im;
             }
-            {
-                // a = -i (-1)^m / (n+1) [ (wx-iwy)(n-m+1)/2 C(m-1) + (wx+iwy)(n+m+1)/2 C(m+1) + wz m C(m) ]
-                T c1re, c1im, c2re, c2im, c3re, c3im;
-                C(nn, m - 1, c1re, c1im);
-                C(nn, m + 1, c2re, c2im);
-                C(nn, m, c3re, c3im);
-                T f1 = (T)(nn - m + 1) * (T)0.5, f2 = (T)(nn + m + 1) * (T)0.5, f3 = wz * (T)m;
-                T sre = f1 * (wmre * c1re - wmim * c1im) + f2 * (wpre * c2re - wpim * c2im) + f3 * c3re;
-                T sim = f1 * (wmre * c1im + wmim * c1re) + f2 * (wpre * c2im + wpim * c2re) + f3 * c3im;
-                T sc = sgn / (T)(nn + 1);
-                // -i (sre + i sim) = sim - i sre; monopole q (eq. 7): phi gains -q g_n^m = -q (-1)^m C(m)
-                acc[0] += sc * sim - qe * sgn * c3re;
-                acc[1] += -sc * sre - qe * sgn * c3im;
-            }
-            if (nn >= 1) {
-                // b = (-1)^m / n [ -1/2 (wx-iwy) C'(m-1) + 1/2 (wx+iwy) C'(m+1) + wz C'(m) ]
-                T c1re, c1im, c2re, c2im, c3re, c3im;
-                C(nn - 1, m - 1, c1re, c1im);
-                C(nn - 1, m + 1, c2re, c2im);
-                C(nn - 1, m, c3re, c3im);
-                T sre = (T)-0.5 * (wmre * c1re - wmim * c1im) + (T)0.5 * (wpre * c2re - wpim * c2im) + wz * c3re;
-                T sim = (T)-0.5 * (wmre * c1im + wmim * c1re) + (T)0.5 * (wpre * c2im + wpim * c2re) + wz * c3im;
-                T sc = sgn / (T)nn;
-                acc[2] += sc * sre;
-                acc[3] += sc * sim;
+            if (SC || qs) {
+                const T qe = wsh[4 * e + 3];
+                acc[6] += qe * re;
+                acc[7] += qe * im;
             }
         }
     }
+    // the sums of all pairs to LDS (over the last chunk's harmonics: p2m_config leaves room for eight)
+    __syncthreads();
+    if (own)
+        for (int k = 0; k < 8; k++) Rre[(size_t)k * TRI + tid] = acc[k];
+    __syncthreads();
     if (!own) return;
+    // conj(Rt_n^k) sums of component c (0, 1, 2: omega; 3: q), with the convention conj(Rt_n^{-1}) = -Rt_n^1
+    // that makes the m >= 1 formulas valid at m = 0 as well
+    auto C = [&](int c, int n2, int kk, T &re, T &im) {
+        re = im = 0;
+        if (n2 < 0 || kk > n2 || (kk == -1 && n2 < 1)) return;
+        const T *S = Rre + (size_t)2 * c * TRI + tri_idx(n2, kk == -1 ? 1 : kk);
+        re = kk == -1 ? -S[0] : S[0];
+        im = -S[TRI];
+    };
+    const T sgn = (m & 1) ? (T)-1 : (T)1;
+    T o[4] = {0, 0, 0, 0};  // Re a, Im a, Re b, Im b
+    // monopole q (eq. 7): phi gains -q g_n^m = -q (-1)^m C(m)
+    T qre, qim;
+    C(3, nn, m, qre, qim);
+    if constexpr (SC) {
+        o[0] = sgn * qre;
+        o[1] = sgn * qim;
+    } else {
+        T xre, xim, yre, yim, zre, zim;
+        {
+            // a = -i (-1)^m / (n+1) [ (wx-iwy)(n-m+1)/2 C(m-1) + (wx+iwy)(n+m+1)/2 C(m+1) + wz m C(m) ]
+            const T f1 = (T)(nn - m + 1) * (T)0.5, f2 = (T)(nn + m + 1) * (T)0.5, f3 = (T)m;
+            C(0, nn, m - 1, xre, xim);
+            C(1, nn, m - 1, yre, yim);
+            T sre = f1 * (xre + yim), sim = f1 * (xim - yre);
+            C(0, nn, m + 1, xre, xim);
+            C(1, nn, m + 1, yre, yim);
+            C(2, nn, m, zre, zim);
+            sre += f2 * (xre - yim) + f3 * zre;
+            sim += f2 * (xim + yre) + f3 * zim;
+            const T sc = sgn / (T)(nn + 1);
+            // -i (sre + i sim) = sim - i sre
+            o[0] = sc * sim - sgn * qre;
+            o[1] = -sc * sre - sgn * qim;
+        }
+        if (nn >= 1) {
+            // b = (-1)^m / n [ -1/2 (wx-iwy) C'(m-1) + 1/2 (wx+iwy) C'(m+1) + wz C'(m) ]
+            C(0, nn - 1, m - 1, xre, xim);
+            C(1, nn - 1, m - 1, yre, yim);
+            T sre = (T)-0.5 * (xre + yim), sim = (T)-0.5 * (xim - yre);
+            C(0, nn - 1, m + 1, xre, xim);
+            C(1, nn - 1, m + 1, yre, yim);
+            C(2, nn - 1, m, zre, zim);
+            sre += (T)0.5 * (xre - yim) + zre;
+            sim += (T)0.5 * (xim + yre) + zim;
+            const T sc = sgn / (T)nn;
+            o[2] = sc * sre;
+            o[3] = sc * sim;
+        }
+    }
     T *out = M + (size_t)b * 2 * P2;
-    out[pk_re(nn, m)] = acc[0] * ih;
-    out[P2 + pk_re(nn, m)] = acc[2] * ih;
+    out[pk_re(nn, m)] = o[0] * ih;
+    out[P2 + pk_re(nn, m)] = o[2] * ih;
     if (m > 0) {
-        out[pk_im(nn, m)] = acc[1] * ih;
-        out[P2 + pk_im(nn, m)] = acc[3] * ih;
+        out[pk_im(nn, m)] = o[1] * ih;
+        out[P2 + pk_im(nn, m)] = o[3] * ih;
     }
 }
 
