@@ -115,7 +115,14 @@ KERNEL_LABEL = {
                "pipelined table reads), one launch per level",
     "qmfma": "k_m2l_qmfma<{p}> (batched M2L on the FP64 matrix cores, vectors in registers), one launch per level",
     "tile": "k_m2l_tile<{t},{p},...> (batched M2L, LDS-tiled target boxes), one launch per level",
+    "rows": "k_m2l_rows<{t},{p}> (batched M2L by quarter turns, vectors split over a wavefront's rows), one launch",
+    "turn": "k_m2l_turn<{t},{p}> (batched M2L by quarter turns, a vector per lane), one launch",
 }
+
+
+def default_m2l(st, p):
+    """the kernel behind a plan's M2L: by quarter turns unless the plan keeps a fixed order of sums"""
+    return st["m2l_kernel"] if st["deterministic"] or p < 7 else "rows" if p > 12 else "turn"
 
 
 def measured_traffic(name):
@@ -461,7 +468,8 @@ def main():
     head, st, (vh, sh) = run_leg(lhf, torch, f"ring4m_fp64_p{p}", x, w, a, p, lhf.FP64, lmax, mx, args.steps,
                                  args.warmup, tune=not args.no_tune)
     ph = head["phases_ms"]
-    launches = sum(1 for l in range(2, len(st["boxes"])) if st["boxes"][l] > 0)
+    kernel = default_m2l(st, p)
+    launches = 1 if kernel in ("rows", "turn") else sum(1 for l in range(2, len(st["boxes"])) if st["boxes"][l] > 0)
     flops = st["n_m2l"] * f_m2l(p)
     achieved = flops / (ph["m2l"] * 1e-3) / 1e12
     out = {
@@ -492,7 +500,7 @@ def main():
         "phase_roofline": head["phase_roofline"],
         "aggregate_roofline": head["aggregate_roofline"],
         "roofline": {
-            "kernel": KERNEL_LABEL.get(head["m2l_kernel"], head["m2l_kernel"]).format(t="double", p=p),
+            "kernel": KERNEL_LABEL.get(kernel, kernel).format(t="double", p=p),
             "bound": "alu",
             "achieved": achieved,
             "peak": PEAK_FP64_TFLOPS,
