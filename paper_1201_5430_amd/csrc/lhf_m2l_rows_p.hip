@@ -51,8 +51,10 @@ __global__ void __launch_bounds__(256 * (tr::waves<T, P>()), (tr::waves<T, P>())
     const int nt = (int)min((int64_t)ns, lv.l[q].off + lv.l[q].nb - b0);
 
     T *wl = (T *)smem;                                   // [4][TY] turns, [2][TH] shift
-    T *trl = wl + 4 * TY + 2 * TH;                       // [NROW][TS] (cos, sin)
-    double *acc = (double *)(trl + 2 * tn::NROW * TS);   // [ns + 1][SS] (last slot absorbs)
+    T *trl = wl + 4 * TY + 2 * TH;                       // [NROW][TS] (cos, sin), one more for odd P
+    double *acc = (double *)(trl + 2 * tn::trig_pairs(P));  // [ns + 1][SS] (last slot absorbs)
+    // the last entry that trigs() reads: slot j = K - 1 of a lane with odd m, in the last row
+    static_assert((tn::NROW - 1) * TS + 2 * (K - 1) + 1 < tn::trig_pairs(P), "angle table");
     int *esrc = (int *)(acc + (size_t)(ns + 1) * SS);
     int *sxyz = esrc + VMAX * ns, *ssys = sxyz + ns;
     int *cnt = ssys + ns;
@@ -60,6 +62,7 @@ __global__ void __launch_bounds__(256 * (tr::waves<T, P>()), (tr::waves<T, P>())
 
     for (int i = tid; i < (4 * TY + 2 * TH) / E; i += NTH) ((V *)wl)[i] = ((const V *)tab)[i];
     for (int i = tid; i < tn::NROW * P; i += NTH) ((V2 *)trl)[i / P * TS + i % P] = ((const V2 *)trig)[i];
+    if ((P & 1) && tid == 0) ((V2 *)trl)[tn::NROW * TS] = V2{0, 0};
     for (int i = tid; i < (ns + 1) * SS; i += NTH) acc[i] = 0.0;
     tn::targets(b0, nt, level, bkey, sxyz, ssys, cnt, tid);
     __syncthreads();

@@ -114,6 +114,9 @@ __host__ __device__ constexpr int src_stride(int p)
 
 constexpr int NPHI = 32, NROW = NPHI + 49;  // rows of the angle table: azimuths, then polar angles
 __host__ __device__ constexpr int trig_stride(int p) { return p | 1; }
+// (cos, sin) pairs of the table where vectors are split over rows: the last pair of orders of an odd p reads
+// m = p as well (and multiplies a zero by it), behind the last row's own entries
+__host__ __device__ constexpr int trig_pairs(int p) { return NROW * trig_stride(p) + (p & 1); }
 
 // target accumulators: entry k of both potentials side by side, one target every acc_stride entries,
 // 2 (1 with a single potential) modulo 32: the lanes of a batch spread over the banks
@@ -307,7 +310,7 @@ constexpr int waves()
 template <typename T>
 inline size_t fixed_bytes(int p, int npot)
 {
-    return sizeof(T) * (tab_size<T>(p) + 2 * tn::NROW * tn::trig_stride(p)) + sizeof(double) * acc_stride(p, npot) + 16;
+    return sizeof(T) * (tab_size<T>(p) + 2 * tn::trig_pairs(p)) + sizeof(double) * acc_stride(p, npot) + 16;
 }
 inline size_t slot_bytes(int p, int npot) { return sizeof(double) * acc_stride(p, npot) + VMAX * 6 + 8; }
 }  // namespace tr
@@ -329,6 +332,8 @@ __host__ __device__ constexpr int tab_size(int p) { return 4 * tr::ytab<T>(p) + 
 // entries of orders 2k, 2k + 1 (one potential), and the length of a stretch in LDS (odd)
 __host__ __device__ constexpr int count(int p, int k) { return 2 * k + 1 < p ? 8 * k + 4 : 4 * k + 1; }
 __host__ __device__ constexpr int stretch(int p) { return (8 * ((p + 1) / 2) - 4) | 1; }
+// (cos, sin) pairs of the eight octants, m = p of the last one included (as tn::trig_pairs)
+__host__ __device__ constexpr int trig_pairs(int p) { return 16 * p + (p & 1); }
 // wavefronts per SIMD
 template <typename T, int P>
 constexpr int waves()
@@ -338,7 +343,7 @@ constexpr int waves()
 template <typename T, int P>
 __host__ __device__ constexpr size_t bytes()
 {
-    return sizeof(T) * (4 * tr::ytab<T>(P) + 2 * htab<T>(P) + 32 * P + 2 * P * P +
+    return sizeof(T) * (4 * tr::ytab<T>(P) + 2 * htab<T>(P) + 2 * trig_pairs(P) + 2 * P * P +
                         4 * (size_t)waves<T, P>() * 16 * stretch(P));
 }
 }  // namespace tm

@@ -40,8 +40,10 @@ __global__ void __launch_bounds__(256 * (tm::waves<T, P>()), (tm::waves<T, P>())
     extern __shared__ __align__(16) char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     T *wl = (T *)smem;                           // [4][TY] turns, [2][TH] shift
-    V2 *trl = (V2 *)(wl + 4 * TY + 2 * TH);      // [octant][azimuth, polar][P] (cos, sin)
-    T *sci = (T *)(trl + 16 * P), *sco = sci + P2;
+    V2 *trl = (V2 *)(wl + 4 * TY + 2 * TH);      // [octant][azimuth, polar][P] (cos, sin), one more for odd P
+    T *sci = (T *)(trl + tm::trig_pairs(P)), *sco = sci + P2;
+    // the last entry that trigs() reads: slot j = K - 1 of a lane with odd m, in the last octant
+    static_assert(15 * P + 2 * (K - 1) + 1 < tm::trig_pairs(P), "angle table");
     T *buf = sco + P2 + wave * 16 * BS;          // the wavefront's stretches: [shift][potential][BS]
     {
         const V *ty = (const V *)tab, *th = (const V *)(tab + 4 * TY + KIND * TH);
@@ -57,6 +59,7 @@ __global__ void __launch_bounds__(256 * (tm::waves<T, P>()), (tm::waves<T, P>())
             const tn::Dir dd = dirs[dx + 3 + 7 * (dy + 3) + 49 * (dz + 3)];
             trl[i] = ((const V2 *)trig)[(size_t)(r < P ? dd.ia : dd.ib) * P + r % P];
         }
+        if ((P & 1) && tid == 0) trl[16 * P] = V2{0, 0};
     }
     __syncthreads();
     const int row = lane >> 4, r0 = row & 1, r1 = row >> 1, part = r1 ^ r0, pot = lane & 1, t = (lane & 15) >> 1;
