@@ -176,6 +176,26 @@ __host__ __device__ constexpr size_t slot_bytes()
 {
     return sizeof(double) * acc_stride(P, NPOT) + VMAX * 6 + 8;
 }
+// where the arrays of a tile of ns targets begin.  The angle table is read by 16-byte (FP32: 8-byte) vectors,
+// so it comes first: behind the accumulators of one potential, an odd number of doubles each, it would begin
+// off their alignment
+struct Lds {
+    size_t trl, acc, esrc, sxyz, ssys, cnt, ecode, end;
+};
+template <typename T, int P, int NPOT>
+__host__ __device__ constexpr Lds lds(int ns)
+{
+    Lds o{};
+    o.trl = 0;
+    o.acc = o.trl + sizeof(T) * 2 * NROW * trig_stride(P);
+    o.esrc = o.acc + sizeof(double) * (size_t)(ns + 1) * acc_stride(P, NPOT);
+    o.sxyz = o.esrc + sizeof(int) * (size_t)VMAX * ns;
+    o.ssys = o.sxyz + sizeof(int) * (size_t)ns;
+    o.cnt = o.ssys + sizeof(int) * (size_t)ns;
+    o.ecode = o.cnt + sizeof(int);
+    o.end = o.ecode + sizeof(uint16_t) * (size_t)VMAX * ns;
+    return o;
+}
 
 // packed coordinates and system of the tile's nt targets
 __device__ inline void targets(int64_t b0, int nt, int level, const uint64_t *__restrict__ bkey, int *sxyz, int *ssys,

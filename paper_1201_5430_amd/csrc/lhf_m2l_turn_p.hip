@@ -45,12 +45,13 @@ __global__ void __launch_bounds__(tn::NTHR, (tn::waves<T, P>())) k_m2l_turn(tn::
     const int64_t b0 = lv.l[q].off + (tile - lv.l[q].tile0) * ns;
     const int nt = (int)min((int64_t)ns, lv.l[q].off + lv.l[q].nb - b0);
 
-    double *acc = (double *)smem;                       // [ns + 1][SS] (last slot absorbs)
-    T *trl = (T *)(acc + (size_t)(ns + 1) * SS);        // [NROW][TS] (cos, sin)
-    int *esrc = (int *)(trl + 2 * tn::NROW * TS);
-    int *sxyz = esrc + VMAX * ns, *ssys = sxyz + ns;
-    int *cnt = ssys + ns;
-    uint16_t *ecode = (uint16_t *)(cnt + 1);
+    const tn::Lds at = tn::lds<T, P, NPOT>(ns);
+    T *trl = (T *)(smem + at.trl);                      // [NROW][TS] (cos, sin)
+    double *acc = (double *)(smem + at.acc);            // [ns + 1][SS] (last slot absorbs)
+    int *esrc = (int *)(smem + at.esrc);
+    int *sxyz = (int *)(smem + at.sxyz), *ssys = (int *)(smem + at.ssys);
+    int *cnt = (int *)(smem + at.cnt);
+    uint16_t *ecode = (uint16_t *)(smem + at.ecode);
 
     for (int i = tid; i < 2 * tn::NROW * P; i += tn::NTHR) {
         const int r = i / (2 * P);
