@@ -1339,7 +1339,8 @@ __device__ __forceinline__ void p2p_finish(int64_t i0, int c, int G, int64_t n, 
 // target left a wavefront's lanes waiting for the fullest of their boxes, and 4,096 targets filled 64
 // wavefronts of the chip: 276 us, now 19; 10,007 elements 520 us, now 66).  The source indices go
 // through LDS; the records are read from L1/L2, the same one by one lane of every target.  Sums of 16
-// pairs enter compensated accumulators; all orders are fixed.
+// pairs enter compensated accumulators; all orders are fixed.  Leaves of more than 64 targets are shared by
+// the gridDim.y workgroups of their column, 64 targets at a time (p2p_split).
 constexpr int P2P_IX = 1024;
 
 template <typename T, bool GRAD, bool Q, int NT>
@@ -1362,6 +1363,7 @@ __global__ void __launch_bounds__(NT) k_p2p(int64_t n, int depth, int64_t leaf_o
     if (lp >= nleaf) return;
     const int lf = (int)(leaf_off + lp);
     const int i0 = bstart[lf], cnt = bcount[lf];
+    if (64 * (int)blockIdx.y >= cnt) return;
     // core radius of the leaf's system (0: singular kernel)
     const T a = (T)sys_a[bkey[lf] >> (3 * depth)];
     const int smooth = a > (T)0;
@@ -1379,47 +1381,52 @@ __global__ void __launch_bounds__(NT) k_p2p(int64_t n, int depth, int64_t leaf_o
     }
     __syncthreads();
     const int S = (what & 2) ? pre[32] : 0;
-    int c;
-    for (int tb = 0; tb < cnt; tb += c) {
-        c = p2p_chunk(cnt - tb);
-        const int G = NT / c, k = tid / c, t = tid - k * c;
-        const bool tact = k < G;
-        const int i = i0 + tb + t;
-        const Rec<T> me = load_rec<false>(xw, i);
-        CompSum<T> acc[NA];
-        for (int j0 = 0; j0 < S; j0 += P2P_IX) {
-            const int m = min(S - j0, P2P_IX);
-            if (j0 > 0 || tb > 0) __syncthreads();  // the previous indices have been read
-            if (tb == 0 || S > P2P_IX)              // one chunk of indices serves every chunk of targets
-                for (int j = tid; j < m; j += NT) {
-                    int lo = 0;
-                    for (int d = 16; d > 0; d >>= 1)
-                        if (pre[lo + d] <= j0 + j) lo += d;
-                    ix[j] = first[lo] + j0 + j - pre[lo];
-                }
-            __syncthreads();
-            if (!tact) continue;
-            for (int j = k; j < m;) {
-                T part[NA];
+    bool again = false;  // not this workgroup's first targets
+    for (int g0 = 64 * (int)blockIdx.y; g0 < cnt; g0 += 64 * (int)gridDim.y) {
+        const int end = min(g0 + 64, cnt);
+        int c;
+        for (int tb = g0; tb < end; tb += c) {
+            c = p2p_chunk(end - tb);
+            const int G = NT / c, k = tid / c, t = tid - k * c;
+            const bool tact = k < G;
+            const int i = i0 + tb + t;
+            const Rec<T> me = load_rec<false>(xw, i);
+            CompSum<T> acc[NA];
+            for (int j0 = 0; j0 < S; j0 += P2P_IX) {
+                const int m = min(S - j0, P2P_IX);
+                if (j0 > 0 || again) __syncthreads();  // the previous indices have been read
+                if (!again || S > P2P_IX)              // one chunk of indices serves every chunk of targets
+                    for (int j = tid; j < m; j += NT) {
+                        int lo = 0;
+                        for (int d = 16; d > 0; d >>= 1)
+                            if (pre[lo + d] <= j0 + j) lo += d;
+                        ix[j] = first[lo] + j0 + j - pre[lo];
+                    }
+                __syncthreads();
+                if (!tact) continue;
+                for (int j = k; j < m;) {
+                    T part[NA];
 #pragma unroll
-                for (int q = 0; q < NA; q++) part[q] = 0;
-                for (int u = 0; u < 16 && j < m; u++, j += G) {
-                    // a wavefront of 64 targets: one source at a time, its record by scalar loads
-                    const int e = c == 64 ? __builtin_amdgcn_readfirstlane(ix[j]) : ix[j];
-                    if (e == i) continue;
-                    const Rec<T> r = load_rec<Q>(xw, e);
-                    if constexpr (GRAD) p2p_pair_grad<T, Q>(r, me.x, me.y, me.z, me.wx, me.wy, me.wz, a, smooth, part);
-                    else
-                        p2p_pair<T, Q>(r, me.x, me.y, me.z, me.wx, me.wy, me.wz, a, smooth, part[0], part[1], part[2],
-                                       part[3], part[4], part[5]);
-                }
+                    for (int q = 0; q < NA; q++) part[q] = 0;
+                    for (int u = 0; u < 16 && j < m; u++, j += G) {
+                        // a wavefront of 64 targets: one source at a time, its record by scalar loads
+                        const int e = c == 64 ? __builtin_amdgcn_readfirstlane(ix[j]) : ix[j];
+                        if (e == i) continue;
+                        const Rec<T> r = load_rec<Q>(xw, e);
+                        if constexpr (GRAD) p2p_pair_grad<T, Q>(r, me.x, me.y, me.z, me.wx, me.wy, me.wz, a, smooth, part);
+                        else
+                            p2p_pair<T, Q>(r, me.x, me.y, me.z, me.wx, me.wy, me.wz, a, smooth, part[0], part[1], part[2],
+                                           part[3], part[4], part[5]);
+                    }
 #pragma unroll
-                for (int q = 0; q < NA; q++) acc[q].add(part[q]);
+                    for (int q = 0; q < NA; q++) acc[q].add(part[q]);
+                }
             }
-        }
 #pragma unroll
-        for (int q = 0; q < NA; q++) red[q * NT + tid] = acc[q].value();
-        p2p_finish<T, GRAD, NT>(i0 + tb, c, G, n, what, red, vfar, perm, vout, sout, gout, bout);
+            for (int q = 0; q < NA; q++) red[q * NT + tid] = acc[q].value();
+            p2p_finish<T, GRAD, NT>(i0 + tb, c, G, n, what, red, vfar, perm, vout, sout, gout, bout);
+            again = true;
+        }
     }
 }
 
@@ -1786,6 +1793,17 @@ static bool p2p_wide(const lhf_plan *P)
     return P->nleaf < P2P_FEW || (P->nleaf < P2P_MANY && P->n >= 8 * P->nleaf);
 }
 
+// Workgroups that share a leaf's targets, 64 at a time (uniform trees; adaptive ones bound their leaves): as many
+// as the fullest leaf has such chunks, as long as a leaf has 2048 pairs for each on average (so
+// that the workgroups of emptier leaves, which read a count and end, stay little beside the pairs).  With one workgroup a leaf 131,072 elements in 64 leaves took 189 ms
+// (FP32 166), now 19.0 (11.9), and 24.2 (18.0) with a lane per target over the whole chip; 524,288 in 512 leaves
+// 64.4 (48.5), now 36.8 (18.7); 200,000 of the ring in a uniform tree of depth 5 9.5 (4.6), now 4.8 (2.1).
+static unsigned p2p_split(const lhf_plan *P)
+{
+    const int64_t chunks = (P->fullest + 63) / 64, share = P->n_p2p / (2048 * P->nleaf);
+    return (unsigned)std::max<int64_t>(1, std::min<int64_t>({chunks, share, 65535}));
+}
+
 template <typename T, bool GRAD, bool Q, int NT>
 static void p2p_launch_t(lhf_plan *P, int what, T *v, T *s, T *g, T *b, hipStream_t st)
 {
@@ -1808,8 +1826,8 @@ static void p2p_launch_t(lhf_plan *P, int what, T *v, T *s, T *g, T *b, hipStrea
 #undef LHF_P2P_TILE
     } else {
         const int64_t nleaf = P->lev[d].nb;
-        hipLaunchKernelGGL((k_p2p<T, GRAD, Q, NT>), dim3((unsigned)((nleaf + 7) / 8 * 8)), dim3(NT), 0, st, n, d,
-                           P->lev[d].off, nleaf, P->ulist, P->bkey, P->bstart, P->bcount, (const T *)P->xw, P->sys_a,
+        hipLaunchKernelGGL((k_p2p<T, GRAD, Q, NT>), dim3((unsigned)((nleaf + 7) / 8 * 8), p2p_split(P)), dim3(NT), 0, st, n,
+                           d, P->lev[d].off, nleaf, P->ulist, P->bkey, P->bstart, P->bcount, (const T *)P->xw, P->sys_a,
                            what, (const T *)P->vfar, P->perm, v, s, g, b);
     }
 }

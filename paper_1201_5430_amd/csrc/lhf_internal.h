@@ -107,6 +107,7 @@ struct lhf_plan {
     int max_per_leaf = 0;
     int max_level = 0;           // deepest level holding a box
     int64_t nleaf = 0;
+    int64_t fullest = 0;         // elements of the fullest leaf, if more than 64 (uniform tree; else 0)
     int64_t n_wx = 0;            // element pairs summed directly for W/X interactions
     int8_t *blev = nullptr;      // [nbox] level of every box
     int32_t *leaves = nullptr;   // [nleaf] leaf boxes in element (Morton) order

@@ -411,7 +411,8 @@ __global__ void k_vcount_map(int64_t off, int64_t nb, int level, const uint64_t 
 
 // U-list (adjacent leaves incl. self) of every leaf, 27 slots
 __global__ void k_ulist(int64_t off, int64_t nb, int level, const uint64_t *__restrict__ bkey,
-                        const int32_t *__restrict__ bcount, int32_t *__restrict__ ulist, int64_t *__restrict__ npairs)
+                        const int32_t *__restrict__ bcount, int32_t *__restrict__ ulist, int64_t *__restrict__ npairs,
+                        int64_t *__restrict__ fullest)
 {
     const int64_t bl = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (bl >= nb) return;
@@ -440,6 +441,7 @@ __global__ void k_ulist(int64_t off, int64_t nb, int level, const uint64_t *__re
             }
     const int64_t me = bcount[off + bl];
     atomicAdd((unsigned long long *)npairs, (unsigned long long)(me * src - me));
+    if (me > 64) atomicMax((unsigned long long *)fullest, (unsigned long long)me);
 }
 
 __global__ void k_sum_i32(int64_t n, const int32_t *__restrict__ a, int64_t *__restrict__ out)
@@ -1325,7 +1327,7 @@ static lhf_status plan_create_t(lhf_plan *P, const void *x, hipStream_t st)
     if (!adaptive) {
         CK(dev_malloc(&P->ulist, sizeof(int32_t) * hnb[d] * 27));
         hipLaunchKernelGGL(k_ulist, grid(hnb[d]), dim3(tpb), 0, st, lt.off[d], hnb[d], d, P->bkey, P->bcount,
-                           P->ulist, dcnt + 1);
+                           P->ulist, dcnt + 1, dcnt + 3);
         hipLaunchKernelGGL(k_add_i32, dim3(nblk), dim3(tpb), 0, st, n, P->eleaf, (int32_t)lt.off[d]);
     } else {
         // levels, the leaf list in element order, the leaf of every element
@@ -1398,6 +1400,7 @@ static lhf_status plan_create_t(lhf_plan *P, const void *x, hipStream_t st)
     P->n_m2l = hc[0];
     P->n_p2p = hc[1];
     P->n_wx = hc[2];
+    P->fullest = adaptive ? 0 : hc[3];
     P->n_m2p = hc[4];
     P->n_p2l = hc[5];
 #undef CK
