@@ -313,9 +313,11 @@ typedef struct {
 } lhf_shapes;
 
 /* Measure the shapes on the plan's own tree and keep the fastest in the plan: one whole
- * evaluation with omega (device [N][3], the plan's precision), then every level's M2L launched
- * once per candidate tile and the adaptive near field once per candidate source tile, timed with
- * HIP events on 'stream'.  With a non-NULL cache_path the shapes are looked up first in, and else
+ * evaluation with omega (device [N][3], the plan's precision), then the M2L as an execute launches
+ * it (quarter turns: all levels at once, one number of targets for all; quarter-vector kernels:
+ * level by level) per candidate tile and the adaptive near field per candidate source tile, timed with
+ * HIP events on 'stream'.  By quarter turns and in the near field the built-in shape is a candidate
+ * and stays unless another is faster by more than repeated launches differ.  With a non-NULL cache_path the shapes are looked up first in, and else
  * appended to, a JSON file keyed by device architecture, precision, p, tree kind, depth and N.
  * Synchronises 'stream', allocates temporary device memory (two [N][3] buffers); the plan's
  * intermediate buffers are left inconsistent, so the next lhf_execute recomputes them (outputs

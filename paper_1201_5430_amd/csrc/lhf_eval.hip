@@ -31,7 +31,9 @@ void m2l_mfma_launch(const lhf_plan *Pl, int level, hipStream_t st);
 void m2l_half_launch(const lhf_plan *Pl, int level, hipStream_t st);
 void turn_stage(const lhf_plan *Pl, bool scalar, hipStream_t st);
 void mm_rows(const lhf_plan *Pl, bool down, int l, hipStream_t st);
-void m2l_turn_launch(const lhf_plan *Pl, bool scalar, int only, hipStream_t st);
+void m2l_turn_launch(const lhf_plan *Pl, bool scalar, hipStream_t st);
+int turn_max_ns(const lhf_plan *Pl);
+int turn_own_ns(const lhf_plan *Pl);
 void m2l_half_stage(const lhf_plan *Pl, int level, hipStream_t st);
 void m2l_quarter_launch(const lhf_plan *Pl, int level, hipStream_t st);
 bool m2l_half_scalar_supported(int precision, int p);
@@ -1867,7 +1869,7 @@ static void translations(lhf_plan *P, hipStream_t st, bool scalar, const std::fu
         // the M2L of every level in one launch, then L2L down the levels adds the parents' expansions
         turn_stage(P, scalar, st);
         mark(7 + 2 * 2);
-        m2l_turn_launch(P, scalar, -1, st);
+        m2l_turn_launch(P, scalar, st);
         mark(8 + 2 * 2);
         for (int l = 3; l <= d; l++) {
             mark(7 + 2 * l);
@@ -2111,11 +2113,15 @@ lhf_status execute_impl(lhf_plan *P, const lhf_io *io, hipStream_t st)
     return execute_t<float>(P, io, st);
 }
 
-// Run-time kernel shapes measured on the plan's own tree: after one whole evaluation (every
-// level's multipoles in place), each level's quarter-vector M2L is launched once per candidate
-// number of targets per tile, and the adaptive near field once per candidate source tile; the
-// fastest of each is kept in the plan.  The timed launches leave the local expansions and the
-// outputs of scratch buffers inconsistent: the next execute recomputes all of them.
+// Run-time kernel shapes measured on the plan's own tree, after one whole evaluation (every level's
+// multipoles in place).  The M2L by quarter turns runs all levels in one launch and is timed so: its tiles
+// share compute units and table loads across levels, and what a level alone prefers (one launch with few
+// tiles: few targets each) made the whole 20% slower than the built-in choice (ring of 4.2 million, p = 23,
+// 286 against 236 ms).  One number of targets serves all levels; the built-in one is a candidate and stays
+// unless another is 2% faster.  The quarter-vector kernels launch once per level and are timed once per
+// level and candidate.  The adaptive near field's source tile: the built-in one unless another is 2% faster.
+// The timed launches leave the local expansions and the outputs of scratch buffers inconsistent: the next
+// execute recomputes all of them.
 template <typename T>
 static lhf_status autotune_t(lhf_plan *P, const T *omega, int *ns, int *ts, hipStream_t st)
 {
@@ -2140,33 +2146,61 @@ static lhf_status autotune_t(lhf_plan *P, const T *omega, int *ns, int *ts, hipS
         io.what = 3;
         rs = execute_t<T>(P, &io, st);
     }
-    auto timed = [&](const std::function<void()> &launch) -> float {
-        float ms = -1.0f;
-        if (rs != LHF_OK) return ms;
-        hipError_t r = hipEventRecord(e0, st);
-        launch();
-        if (r == hipSuccess) r = hipEventRecord(e1, st);
-        if (r == hipSuccess) r = hipEventSynchronize(e1);
-        if (r == hipSuccess) r = hipEventElapsedTime(&ms, e0, e1);
-        if (r != hipSuccess) fail(r, "autotune timing");
-        return ms;
+    auto timed = [&](const std::function<void()> &launch, int reps) -> float {
+        float best = -1.0f;
+        for (int k = 0; k < reps && rs == LHF_OK; k++) {
+            float ms = -1.0f;
+            hipError_t r = hipEventRecord(e0, st);
+            launch();
+            if (r == hipSuccess) r = hipEventRecord(e1, st);
+            if (r == hipSuccess) r = hipEventSynchronize(e1);
+            if (r == hipSuccess) r = hipEventElapsedTime(&ms, e0, e1);
+            if (r != hipSuccess) fail(r, "autotune timing");
+            else if (best < 0 || ms < best) best = ms;
+        }
+        return best;
     };
     for (int l = 0; l <= MAXDEPTH; l++) ns[l] = 0;
     const int maxns = m2l_tile_range(P);
-    if (P->use_turn) turn_stage(P, false, st);
-    for (int l = 2; l <= P->depth && maxns > 0 && rs == LHF_OK; l++) {
+    auto all = [&](int c) {
+        for (int l = 2; l <= P->depth; l++) P->m2l_ns[l] = P->lev[l].nb ? c : 0;
+    };
+    if (P->use_turn && maxns > 0 && rs == LHF_OK) {
+        turn_stage(P, false, st);
+        const auto launch = [&] { m2l_turn_launch(P, false, st); };
+        all(0);  // the built-in number
+        int best = turn_own_ns(P);
+        timed(launch, 1);
+        float tbest = timed(launch, 3);
+        if (best > maxns) best = 0;  // not a number that a caller may ask for: named as built-in
+        for (int c : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16}) {
+            if (c > std::min(maxns, turn_max_ns(P))) break;
+            if (c == best) continue;
+            all(c);
+            float t = timed(launch, 1);
+            if (t >= 0 && t < 1.1f * tbest) t = std::min(t, timed(launch, 2));
+            if (t >= 0 && t < 0.98f * tbest) {
+                best = c;
+                tbest = t;
+            }
+        }
+        all(best);
+        for (int l = 2; l <= P->depth; l++) ns[l] = P->m2l_ns[l];
+    }
+    for (int l = 2; l <= P->depth && !P->use_turn && maxns > 0 && rs == LHF_OK; l++) {
         if (P->lev[l].nb == 0) continue;
-        if (!P->use_turn) m2l_quarter_stage(P, l, st);
+        m2l_quarter_stage(P, l, st);
         int best = 0;
         float tbest = 0;
         for (int c : {1, 2, 3, 4, 6, 8, 10, 12, 16}) {
             if (c > maxns) break;
             P->m2l_ns[l] = c;
-            const float t = timed([&] {
-                if (P->use_turn) m2l_turn_launch(P, false, l, st);
-                else if (P->use_qmfma) m2l_qmfma_launch(P, l, st);
-                else m2l_quarter_launch(P, l, st);
-            });
+            const float t = timed(
+                [&] {
+                    if (P->use_qmfma) m2l_qmfma_launch(P, l, st);
+                    else m2l_quarter_launch(P, l, st);
+                },
+                1);
             if (t >= 0 && (best == 0 || t < tbest)) {
                 best = c;
                 tbest = t;
@@ -2176,12 +2210,16 @@ static lhf_status autotune_t(lhf_plan *P, const T *omega, int *ns, int *ts, hipS
     }
     *ts = 0;
     if (P->adaptive && P->nleaf > 0 && rs == LHF_OK) {
-        int best = 0;
-        float tbest = 0;
-        for (int c : {64, 128, 256}) {
+        const auto launch = [&] { p2p_launch<T, false, false>(P, 2, v, s, nullptr, nullptr, st); };
+        int best = P2P_TS;
+        P->p2p_ts = best;
+        timed(launch, 1);
+        float tbest = timed(launch, 3);
+        for (int c : {64, 256}) {
             P->p2p_ts = c;
-            const float t = timed([&] { p2p_launch<T, false, false>(P, 2, v, s, nullptr, nullptr, st); });
-            if (t >= 0 && (best == 0 || t < tbest)) {
+            timed(launch, 1);
+            const float t = timed(launch, 3);
+            if (t >= 0 && t < 0.98f * tbest) {
                 best = c;
                 tbest = t;
             }

@@ -299,15 +299,12 @@ __global__ void __launch_bounds__(256 * (tr::waves<T, P>()), (tr::waves<T, P>())
 }
 
 template <typename T, int P, bool SC>
-static void launch(const lhf_plan *Pl, int only, hipStream_t st)
+static void launch(const lhf_plan *Pl, hipStream_t st)
 {
     constexpr int NPOT = SC ? 1 : 2, NTH = 256 * tr::waves<T, P>();
     const size_t fixed = tr::fixed_bytes<T>(P, NPOT), each = tr::slot_bytes(P, NPOT);
-    const int mx = (int)std::min<size_t>(60, (163840 - fixed) / each);
-    int64_t nb = 0;
-    for (int l = 2; l <= Pl->depth; l++) nb += Pl->lev[l].nb;
-    const int ns = (int)std::max<int64_t>(1, std::min<int64_t>(mx, nb / 512));
-    const tn::Levels lv = tn::levels(Pl, ns, mx, only);
+    const int mx = tr::max_ns<T>(P, NPOT), ns = tr::own_ns(Pl, mx);
+    const tn::Levels lv = tn::levels(Pl, ns, mx);
     if (lv.ntiles == 0) return;
     k_m2l_rows<T, P, SC><<<dim3((unsigned)((lv.ntiles + 7) / 8 * 8)), dim3(NTH), fixed + tn::max_ns(lv) * each, st>>>(
         lv, Pl->bkey, (const T *)Pl->l2pv, (T *)Pl->Lc, (const T *)Pl->ttab, (const T *)Pl->ttrig,
@@ -324,13 +321,13 @@ hipError_t rows_attr()
 }
 
 template <typename T, int P>
-void rows_launch(const lhf_plan *Pl, bool scalar, int only, hipStream_t st)
+void rows_launch(const lhf_plan *Pl, bool scalar, hipStream_t st)
 {
-    if (scalar) launch<T, P, true>(Pl, only, st);
-    else launch<T, P, false>(Pl, only, st);
+    if (scalar) launch<T, P, true>(Pl, st);
+    else launch<T, P, false>(Pl, st);
 }
 
 template hipError_t rows_attr<LHF_TURN_T, LHF_TURN_P>();
-template void rows_launch<LHF_TURN_T, LHF_TURN_P>(const lhf_plan *, bool, int, hipStream_t);
+template void rows_launch<LHF_TURN_T, LHF_TURN_P>(const lhf_plan *, bool, hipStream_t);
 
 }  // namespace lhf

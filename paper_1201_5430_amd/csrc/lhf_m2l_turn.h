@@ -248,15 +248,15 @@ __device__ inline void translations(int nt, int side, const int32_t *__restrict_
     }
 }
 
-// tiles of ns consecutive boxes over the levels, the deepest first (only >= 0: that level alone); a tuned
-// number of targets of a level (at most mx) goes before ns
-inline Levels levels(const lhf_plan *Pl, int ns, int mx, int only)
+// tiles of ns consecutive boxes over the levels, the deepest first; a tuned number of targets of a level (at
+// most mx) goes before ns
+inline Levels levels(const lhf_plan *Pl, int ns, int mx)
 {
     Levels lv;
     lv.n = 0;
     lv.ntiles = 0;
     for (int l = Pl->depth; l >= 2; l--) {
-        if (Pl->lev[l].nb == 0 || (only >= 0 && l != only)) continue;
+        if (Pl->lev[l].nb == 0) continue;
         const int k = Pl->m2l_ns[l] > 0 ? std::min(Pl->m2l_ns[l], mx) : ns;
         lv.l[lv.n] = {lv.ntiles, Pl->lev[l].off, Pl->lev[l].nb, Pl->dmap[l], k};
         lv.level[lv.n++] = l;
@@ -333,6 +333,18 @@ inline size_t fixed_bytes(int p, int npot)
     return sizeof(T) * (tab_size<T>(p) + 2 * tn::trig_pairs(p)) + sizeof(double) * acc_stride(p, npot) + 16;
 }
 inline size_t slot_bytes(int p, int npot) { return sizeof(double) * acc_stride(p, npot) + VMAX * 6 + 8; }
+// targets per tile: as many as the LDS holds, fewer where that would leave compute units without a tile
+template <typename T>
+inline int max_ns(int p, int npot)
+{
+    return (int)std::min<size_t>(60, (163840 - fixed_bytes<T>(p, npot)) / slot_bytes(p, npot));
+}
+inline int own_ns(const lhf_plan *Pl, int mx)
+{
+    int64_t nb = 0;
+    for (int l = 2; l <= Pl->depth; l++) nb += Pl->lev[l].nb;
+    return (int)std::max<int64_t>(1, std::min<int64_t>(mx, nb / 512));
+}
 }  // namespace tr
 
 // M2M and L2L in the same split (lhf_mm_rows_p.hip)
@@ -372,11 +384,11 @@ __host__ __device__ constexpr size_t bytes()
 template <typename T, int P>
 hipError_t turn_attr();
 template <typename T, int P>
-void turn_launch(const lhf_plan *Pl, bool scalar, int only, hipStream_t st);
+void turn_launch(const lhf_plan *Pl, bool scalar, hipStream_t st);
 template <typename T, int P>
 hipError_t rows_attr();
 template <typename T, int P>
-void rows_launch(const lhf_plan *Pl, bool scalar, int only, hipStream_t st);
+void rows_launch(const lhf_plan *Pl, bool scalar, hipStream_t st);
 template <typename T, int P>
 hipError_t mm_rows_attr();
 template <typename T, int P>

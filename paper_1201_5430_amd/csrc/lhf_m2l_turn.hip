@@ -376,13 +376,12 @@ void turn_stage(const lhf_plan *Pl, bool scalar, hipStream_t st)
     else scalar ? stage_t<float, 1>(Pl, st) : stage_t<float, 2>(Pl, st);
 }
 
-// only >= 0: the boxes of that level alone
-void m2l_turn_launch(const lhf_plan *Pl, bool scalar, int only, hipStream_t st)
+void m2l_turn_launch(const lhf_plan *Pl, bool scalar, hipStream_t st)
 {
 #define F(N) \
-    if (Pl->p == N) return turn_launch<T, N>(Pl, scalar, only, st);
+    if (Pl->p == N) return turn_launch<T, N>(Pl, scalar, st);
 #define G(N) \
-    if (Pl->p == N) return rows_launch<T, N>(Pl, scalar, only, st);
+    if (Pl->p == N) return rows_launch<T, N>(Pl, scalar, st);
     if (Pl->precision == LHF_FP64) {
         using T = double;
         LHF_TURN_FP64(F) LHF_ROWS_FP64(G)
@@ -393,6 +392,13 @@ void m2l_turn_launch(const lhf_plan *Pl, bool scalar, int only, hipStream_t st)
 #undef F
 #undef G
 }
+
+// targets per tile of the rows kernel: the most that it holds, and what it takes unless told otherwise
+int turn_max_ns(const lhf_plan *Pl)
+{
+    return Pl->precision == LHF_FP64 ? tr::max_ns<double>(Pl->p, 2) : tr::max_ns<float>(Pl->p, 2);
+}
+int turn_own_ns(const lhf_plan *Pl) { return tr::own_ns(Pl, turn_max_ns(Pl)); }
 
 // M2M into the boxes of level l (down: L2L into them, added to what they hold)
 void mm_rows(const lhf_plan *Pl, bool down, int l, hipStream_t st)

@@ -246,7 +246,7 @@ __global__ void __launch_bounds__(tn::NTHR, (tn::waves<T, P>())) k_m2l_turn(tn::
 // targets per tile: as many as the LDS takes (one workgroup per compute unit and wavefront of a SIMD),
 // fewer where that would leave compute units without a tile
 template <typename T, int P, bool SC>
-static void launch(const lhf_plan *Pl, int only, hipStream_t st)
+static void launch(const lhf_plan *Pl, hipStream_t st)
 {
     constexpr int NPOT = SC ? 1 : 2, WGS = tn::waves<T, P>();  // workgroups per compute unit
     constexpr size_t fixed = tn::fixed_bytes<T, P, NPOT>(), each = tn::slot_bytes<T, P, NPOT>();
@@ -254,7 +254,7 @@ static void launch(const lhf_plan *Pl, int only, hipStream_t st)
     int64_t nb = 0;
     for (int l = 2; l <= Pl->depth; l++) nb += Pl->lev[l].nb;
     const int ns = (int)std::max<int64_t>(1, std::min<int64_t>(mx, nb / (512 * WGS)));
-    const tn::Levels lv = tn::levels(Pl, ns, mx, only);
+    const tn::Levels lv = tn::levels(Pl, ns, mx);
     if (lv.ntiles == 0) return;
     k_m2l_turn<T, P, SC><<<dim3((unsigned)((lv.ntiles + 7) / 8 * 8)), dim3(tn::NTHR), fixed + tn::max_ns(lv) * each, st>>>(
         lv, Pl->bkey, (const T *)Pl->l2pv, (T *)Pl->Lc, (const T *)Pl->ttab, (const T *)Pl->ttrig,
@@ -272,13 +272,13 @@ hipError_t turn_attr()
 }
 
 template <typename T, int P>
-void turn_launch(const lhf_plan *Pl, bool scalar, int only, hipStream_t st)
+void turn_launch(const lhf_plan *Pl, bool scalar, hipStream_t st)
 {
-    if (scalar) launch<T, P, true>(Pl, only, st);
-    else launch<T, P, false>(Pl, only, st);
+    if (scalar) launch<T, P, true>(Pl, st);
+    else launch<T, P, false>(Pl, st);
 }
 
 template hipError_t turn_attr<LHF_TURN_T, LHF_TURN_P>();
-template void turn_launch<LHF_TURN_T, LHF_TURN_P>(const lhf_plan *, bool, int, hipStream_t);
+template void turn_launch<LHF_TURN_T, LHF_TURN_P>(const lhf_plan *, bool, hipStream_t);
 
 }  // namespace lhf
