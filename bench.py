@@ -108,7 +108,7 @@ def phase_roofline(st, ph, p, prec, n):
                  "peak_alu_tflops": peak, "peak_hbm_gbs": PEAK_HBM_GBS}
 
 
-# the dominant kernel of the headline per M2L kernel family the plan chose
+# the dominant kernel of the headline per M2L kernel that the plan runs
 KERNEL_LABEL = {
     "half": "k_m2l_half<{t},{p}> (batched M2L, half-vector lanes, rotation tables from L2), one launch per level",
     "quarter": "k_m2l_quarter<{p}> (batched M2L, quarter-vector lanes, class rotation tables staged in LDS, "
@@ -118,11 +118,6 @@ KERNEL_LABEL = {
     "rows": "k_m2l_rows<{t},{p}> (batched M2L by quarter turns, vectors split over a wavefront's rows), one launch",
     "turn": "k_m2l_turn<{t},{p}> (batched M2L by quarter turns, a vector per lane), one launch",
 }
-
-
-def default_m2l(st, p):
-    """the kernel behind a plan's M2L: by quarter turns unless the plan keeps a fixed order of sums"""
-    return st["m2l_kernel"] if st["deterministic"] or p < 7 else "rows" if p > 12 else "turn"
 
 
 def measured_traffic(name):
@@ -194,7 +189,7 @@ def run_leg(lhf, torch, name, x, w, a, p, prec, depth, max_per_leaf, steps, warm
     res = {"workload": name, "n": n, "p": p, "precision": "fp64" if prec == lhf.FP64 else "fp32",
            "steps": steps, "ms_per_step": ms, "elements_per_s": n / (ms * 1e-3), "execute_ms": exec_ms,
            "plan_ms": ms - exec_ms, "execute_only_elements_per_s": n / (exec_ms * 1e-3), "phases_ms": phases,
-           "m2l_kernel": st["m2l_kernel"], "m2l_achieved_tflops": m2l_tf,
+           "m2l_kernel": st["m2l_runs"], "m2l_achieved_tflops": m2l_tf,
            "counts": {"boxes": st["boxes"], "leaves": st["n_leaves"], "m2l": st["n_m2l"], "m2m": st["n_m2m"],
                       "u_pairs": st["n_p2p_pairs"], "wx_pairs": st["n_wx_pairs"], "m2p_pairs": st["n_m2p"],
                       "p2l_pairs": st["n_p2l"]}}
@@ -468,7 +463,7 @@ def main():
     head, st, (vh, sh) = run_leg(lhf, torch, f"ring4m_fp64_p{p}", x, w, a, p, lhf.FP64, lmax, mx, args.steps,
                                  args.warmup, tune=not args.no_tune)
     ph = head["phases_ms"]
-    kernel = default_m2l(st, p)
+    kernel = st["m2l_runs"]
     launches = 1 if kernel in ("rows", "turn") else sum(1 for l in range(2, len(st["boxes"])) if st["boxes"][l] > 0)
     flops = st["n_m2l"] * f_m2l(p)
     achieved = flops / (ph["m2l"] * 1e-3) / 1e12

@@ -97,7 +97,8 @@ typedef enum { LHF_FP64 = 0, LHF_FP32 = 1 } lhf_precision;
  * the others force one and return LHF_ERR_UNSUPPORTED where it has no instantiation.  From p = 7 on,
  * where the dense box maps allow (depth <= 8) and LHF_DETERMINISTIC is not asked, AUTO runs the M2L by
  * quarter turns (every order, all levels in one launch; LDS atomics, so lhf_stats.deterministic is 0) in
- * place of the kernel it would otherwise take; lhf_stats.m2l_kernel keeps that kernel's name. */
+ * place of the kernel it would otherwise take.  lhf_stats.m2l_kernel keeps that kernel's name (a caller can
+ * ask for it by that value); lhf_plan_kernels names the kernels that run. */
 #define LHF_M2L_AUTO 0
 #define LHF_M2L_HALF 1         /* batched VALU, each coefficient vector split over two lanes by the
                                   parity of m: p = 8, 10, 12, 16 (FP64 also 20, 22, 23, 24) */
@@ -114,13 +115,21 @@ typedef enum { LHF_FP64 = 0, LHF_FP32 = 1 } lhf_precision;
                                   in registers in the instruction's operand layout (residue m mod 4 per
                                   lane, both parts, eight translations per wavefront): FP64 p = 20, 22,
                                   23, 24 */
+/* reported by lhf_plan_kernels; a descriptor gets them by AUTO */
+#define LHF_M2L_TURN 8         /* by quarter turns, a whole coefficient vector per lane: FP64 p = 7..12,
+                                  FP32 p = 7..16 */
+#define LHF_M2L_ROWS 9         /* by quarter turns, each vector split over a wavefront's four rows: FP64
+                                  p = 13..24 */
 
 /* M2M / L2L kernel (lhf_desc.mm_kernel) */
 #define LHF_MM_AUTO 0
 #define LHF_MM_HALF 1          /* batched, eight child shifts per wavefront: p = 8, 10, 12, 16 */
 #define LHF_MM_GENERIC 2       /* one wavefront per parent (M2M) or child (L2L): any p */
 #define LHF_MM_QUARTER 3       /* batched, four child shifts per wavefront, each vector over four lanes
-                                  by m mod 4: FP64 p = 20, 22, 23, 24 (the default there) */
+                                  by m mod 4: FP64 p = 20, 22, 23, 24 */
+/* reported by lhf_plan_kernels; a descriptor gets it by AUTO, beside the M2L by quarter turns */
+#define LHF_MM_ROWS 4          /* by quarter turns, eight shifts per wavefront, each vector split over its
+                                  four rows: p = 7..24 (FP32 ..16) */
 
 typedef struct {
     int32_t p;            /* truncation number, orders n = 0..p-1 (Sec. 5.1); 0: the smallest order
@@ -152,8 +161,9 @@ typedef struct {
     int64_t n_leaves;          /* leaf boxes */
     int64_t n_wx_pairs;        /* adaptive tree: element pairs of W/X interactions summed directly
                                   with the singular kernel (ordered; those not taken by M2P / P2L) */
-    int32_t m2l_kernel;        /* the M2L kernel the plan runs (LHF_M2L_*, never AUTO) */
-    int32_t mm_kernel;         /* the M2M/L2L kernel (LHF_MM_HALF, LHF_MM_GENERIC or LHF_MM_QUARTER) */
+    int32_t m2l_kernel;        /* the M2L kernel asked for, or the one that AUTO takes where it does not
+                                  run by quarter turns (LHF_M2L_*, never AUTO; see lhf_plan_kernels) */
+    int32_t mm_kernel;         /* likewise M2M/L2L (LHF_MM_HALF, LHF_MM_GENERIC or LHF_MM_QUARTER) */
     int32_t deterministic;     /* 1 if every kernel of the plan accumulates in a fixed order */
     int32_t p_from_tol;        /* 1 if p was chosen from tol */
     double calib_err_v;        /* calibrated relative L2 error of v and of s at the plan's p for its */
@@ -274,6 +284,10 @@ lhf_status lhf_evaluate_noalloc(const lhf_desc *d, int64_t n, const void *x, con
 
 /* Counts of the plan (boxes, translations, near-field pairs). */
 lhf_status lhf_plan_stats(const lhf_plan *plan, lhf_stats *out);
+
+/* The kernels that the plan's executes launch: M2L (LHF_M2L_*, TURN and ROWS among them) and M2M/L2L
+ * (LHF_MM_*, ROWS among them); never AUTO.  Either pointer may be NULL. */
+lhf_status lhf_plan_kernels(const lhf_plan *plan, int32_t *m2l, int32_t *mm);
 
 /* Release the plan (synchronises the device first: executes may be queued on any stream).
  * Its device blocks stay with the library and serve the next plan that asks for the same

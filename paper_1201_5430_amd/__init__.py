@@ -25,6 +25,10 @@ TRANS_RCR, TRANS_DIRECT = 0, 1
 M2L_AUTO, M2L_HALF, M2L_TILE, M2L_TILE1, M2L_MFMA, M2L_GENERIC, M2L_QUARTER, M2L_QMFMA = range(8)
 MM_AUTO, MM_HALF, MM_GENERIC, MM_QUARTER = range(4)
 M2L_NAMES = ("auto", "half", "tile", "tile1", "mfma", "generic", "quarter", "qmfma")
+MM_NAMES = ("auto", "half", "generic", "quarter")
+#: kernels that a plan runs (the last ones by AUTO alone)
+M2L_RUNS = M2L_NAMES + ("turn", "rows")
+MM_RUNS = MM_NAMES + ("rows",)
 STATUS = {0: "LHF_OK", 1: "LHF_WARN_CORE_SPLIT", 2: "LHF_WARN_TOL_UNMET", -1: "LHF_ERR_ARG",
           -2: "LHF_ERR_DOMAIN", -3: "LHF_ERR_NONFINITE", -4: "LHF_ERR_WORKSPACE", -5: "LHF_ERR_HIP",
           -6: "LHF_ERR_UNSUPPORTED", -7: "LHF_ERR_STATE"}
@@ -36,7 +40,7 @@ EXPORTS = ("lhf_desc_default", "lhf_plan_create", "lhf_plan_create_multi", "lhf_
            "lhf_batch_create", "lhf_batch_execute", "lhf_batch_info", "lhf_batch_destroy",
            "lhf_release_cached_memory", "lhf_evaluate_noalloc", "lhf_execute_io", "lhf_execute_scalar",
            "lhf_filament_create", "lhf_filament_execute", "lhf_filament_plan", "lhf_filament_destroy",
-           "lhf_plan_autotune", "lhf_plan_set_shapes", "lhf_plan_get_shapes")
+           "lhf_plan_autotune", "lhf_plan_set_shapes", "lhf_plan_get_shapes", "lhf_plan_kernels")
 PHASES = ("gather", "p2m", "m2m", "down", "l2p", "p2p", "m2l")
 
 
@@ -113,6 +117,8 @@ def load():
         L.lhf_evaluate_noalloc.restype = C.c_int
         L.lhf_plan_stats.argtypes = [vp, C.POINTER(Stats)]
         L.lhf_plan_stats.restype = C.c_int
+        L.lhf_plan_kernels.argtypes = [vp, C.POINTER(C.c_int32), C.POINTER(C.c_int32)]
+        L.lhf_plan_kernels.restype = C.c_int
         L.lhf_plan_destroy.argtypes = [vp]
         L.lhf_plan_destroy.restype = C.c_int
         L.lhf_release_cached_memory.argtypes = []
@@ -290,13 +296,16 @@ class Plan:
         return phi, grad
 
     def stats(self):
-        st = Stats()
+        """counts of the plan; m2l_runs and mm_runs name the kernels that its executes launch, m2l_kernel and
+        mm_kernel those asked for (or taken where the order does not run by quarter turns)"""
+        st, m2l, mm = Stats(), C.c_int32(), C.c_int32()
         _check(load().lhf_plan_stats(self._h, C.byref(st)))
-        return dict(n=st.n, depth=st.depth, p=st.p, boxes=list(st.boxes[:st.depth + 1]), n_m2l=st.n_m2l,
+        _check(load().lhf_plan_kernels(self._h, C.byref(m2l), C.byref(mm)))
+        return dict(m2l_runs=M2L_RUNS[m2l.value], mm_runs=MM_RUNS[mm.value], n=st.n, depth=st.depth, p=st.p, boxes=list(st.boxes[:st.depth + 1]), n_m2l=st.n_m2l,
                     n_m2m=st.n_m2m, n_l2l=st.n_l2l, n_p2p_pairs=st.n_p2p_pairs,
                     n_theta_classes=st.n_theta_classes, max_level=st.max_level, n_leaves=st.n_leaves,
                     n_wx_pairs=st.n_wx_pairs, m2l_kernel=M2L_NAMES[st.m2l_kernel],
-                    mm_kernel=("auto", "half", "generic", "quarter")[st.mm_kernel], deterministic=bool(st.deterministic),
+                    mm_kernel=MM_NAMES[st.mm_kernel], deterministic=bool(st.deterministic),
                     p_from_tol=bool(st.p_from_tol), calib_err_v=st.calib_err_v, calib_err_s=st.calib_err_s,
                     warnings=st.warnings, wx_expansions=bool(st.wx_expansions), n_m2p=st.n_m2p, n_p2l=st.n_p2l)
 

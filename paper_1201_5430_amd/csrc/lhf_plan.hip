@@ -1643,6 +1643,12 @@ lhf_status plan_new(lhf_plan **out, const lhf_desc *d, int nsys, const int64_t *
 
 void plan_free(lhf_plan *P) { free_plan(P); }
 
+// the M2L kernel that executes launch
+static int m2l_runs(const lhf_plan *P)
+{
+    return !P->use_turn ? P->m2l_kind : P->turn_rows ? LHF_M2L_ROWS : LHF_M2L_TURN;
+}
+
 // targets per M2L tile that a caller may ask for (0: the plan's kernel has one shape)
 int m2l_tile_range(const lhf_plan *P)
 {
@@ -1854,6 +1860,14 @@ lhf_status lhf_plan_stats(const lhf_plan *P, lhf_stats *out)
     out->wx_expansions = P->wx_exp ? 1 : 0;
     out->n_m2p = P->n_m2p;
     out->n_p2l = P->n_p2l;
+    return LHF_OK;
+}
+
+lhf_status lhf_plan_kernels(const lhf_plan *P, int32_t *m2l, int32_t *mm)
+{
+    if (!P) return arg_error("plan is NULL");
+    if (m2l) *m2l = m2l_runs(P);
+    if (mm) *mm = P->use_mmrows ? LHF_MM_ROWS : P->mm_kind;
     return LHF_OK;
 }
 
