@@ -317,12 +317,14 @@ lhf_status lhf_profile_end(lhf_plan *plan, double *phase_ms, int32_t *n_exec);
 /* ---- Run-time kernel shapes of a plan (autotuner) ----
  *
  * Shapes the library can choose at run time without rebuilding the plan: the number of target
- * boxes per workgroup tile of the quarter-vector M2L kernel at every level (FP64 p = 16-24;
- * 1 .. 6 at p = 23, more at lower orders, as the LDS allows), and the number of source elements
+ * boxes per workgroup tile of the M2L at every level (by quarter turns at FP64 p = 16, 20, 22-24; the
+ * quarter-vector and the register matrix-core kernel wherever they are asked for; 1 .. 6 at p = 23, more at
+ * lower orders), and the number of source elements
  * staged per LDS tile by the adaptive near-field kernel (64, 128 or 256; v and s outputs only:
  * with grad_v, beta or monopoles the kernel keeps 128).  0 means the built-in choice. */
 typedef struct {
-    int32_t m2l_tile[9];  /* [level 0 .. 8]; 0: built-in (as many targets as fit, at least ~1024 tiles) */
+    int32_t m2l_tile[9];  /* [level 0 .. 8]; 0: built-in (as many targets as fit, at least ~1024 tiles,
+                             by quarter turns ~512) */
     int32_t p2p_tile;     /* 0: built-in (128) */
 } lhf_shapes;
 
@@ -332,7 +334,8 @@ typedef struct {
  * level by level) per candidate tile and the adaptive near field per candidate source tile, timed with
  * HIP events on 'stream'.  By quarter turns and in the near field the built-in shape is a candidate
  * and stays unless another is faster by more than repeated launches differ.  With a non-NULL cache_path the shapes are looked up first in, and else
- * appended to, a JSON file keyed by device architecture, precision, p, tree kind, depth and N.
+ * appended to, a JSON file keyed by device architecture, precision, p, tree kind, depth, N and
+ * the M2L kernel that runs.
  * Synchronises 'stream', allocates temporary device memory (two [N][3] buffers); the plan's
  * intermediate buffers are left inconsistent, so the next lhf_execute recomputes them (outputs
  * are only ever written by lhf_execute).  out may be NULL. */

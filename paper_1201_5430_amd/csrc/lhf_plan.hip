@@ -1476,8 +1476,9 @@ bool kernel_deterministic(int precision, int p, int k)
 
 static const char *m2l_name(int k)
 {
-    static const char *nm[] = {"AUTO", "HALF", "TILE", "TILE1", "MFMA", "GENERIC", "QUARTER", "QMFMA"};
-    return (k >= 0 && k <= 7) ? nm[k] : "?";
+    static const char *nm[] = {"AUTO",    "HALF",    "TILE",  "TILE1", "MFMA",
+                               "GENERIC", "QUARTER", "QMFMA", "TURN",  "ROWS"};
+    return (k >= 0 && k <= LHF_M2L_ROWS) ? nm[k] : "?";
 }
 
 // Resolve the descriptor's kernel requests (host only, before any launch).  AUTO takes the
@@ -1936,11 +1937,12 @@ static std::string shapes_key(const lhf_plan *P)
         if (c != std::string::npos) arch = arch.substr(0, c);
     }
     return arch + "/" + (P->precision == LHF_FP64 ? "fp64" : "fp32") + "/p" + std::to_string(P->p) + "/" +
-           (P->adaptive ? "adaptive" : "uniform") + "/d" + std::to_string(P->depth) + "/n" + std::to_string(P->n);
+           (P->adaptive ? "adaptive" : "uniform") + "/d" + std::to_string(P->depth) + "/n" + std::to_string(P->n) + "/" +
+           m2l_name(m2l_runs(P));  // another kernel holds other numbers of targets, or one shape only
 }
 
 // shapes cache: a JSON array with one object per line
-//   {"key": "gfx950/fp64/p23/adaptive/d8/n4194304", "m2l_tile": [0, 0, 1, 1, 4, 6, 6, 6, 6], "p2p_tile": 128}
+//   {"key": "gfx950/fp64/p23/adaptive/d8/n4194304/ROWS", "m2l_tile": [0, 0, 5, 5, 5, 5, 5, 5, 5], "p2p_tile": 256}
 static bool read_shapes(const char *path, const std::string &key, lhf_shapes *out, std::vector<std::string> *lines)
 {
     FILE *f = fopen(path, "r");
