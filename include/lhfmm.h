@@ -319,7 +319,7 @@ lhf_status lhf_profile_end(lhf_plan *plan, double *phase_ms, int32_t *n_exec);
  * Shapes the library can choose at run time without rebuilding the plan: the number of target
  * boxes per workgroup tile of the M2L at every level (by quarter turns at FP64 p = 16, 20, 22-24; the
  * quarter-vector and the register matrix-core kernel wherever they are asked for; 1 .. 6 at p = 23, more at
- * lower orders), and the number of source elements
+ * lower orders; a plan keeps what its kernel holds: by quarter turns 5 at p = 23), and the number of source elements
  * staged per LDS tile by the adaptive near-field kernel (64, 128 or 256; v and s outputs only:
  * with grad_v, beta or monopoles the kernel keeps 128).  0 means the built-in choice. */
 typedef struct {

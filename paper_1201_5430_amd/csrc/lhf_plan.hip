@@ -39,6 +39,7 @@ bool mmhalf_build(lhf_plan *Pl, hipStream_t st);
 int turn_kind(int precision, int p);
 bool turn_build(lhf_plan *Pl, hipStream_t st);
 size_t turn_src_values(const lhf_plan *Pl);
+int turn_max_ns(const lhf_plan *Pl);
 bool wmfma_build(lhf_plan *Pl, hipStream_t st);
 
 bool m2l_tile_owned(int precision, int p);
@@ -1984,7 +1985,10 @@ lhf_status lhf_plan_set_shapes(lhf_plan *P, const lhf_shapes *sh)
     if (!P || !sh) return arg_error("plan and shapes must be non-NULL");
     lhf_status s = check_shapes(P, sh);
     if (s != LHF_OK) return s;
-    for (int l = 0; l < LHF_SHAPE_LEVELS; l++) P->m2l_ns[l] = sh->m2l_tile[l];
+    // what is kept, and read back, is what runs: the M2L by quarter turns may hold fewer targets than the
+    // range that callers know
+    const int mx = P->use_turn ? turn_max_ns(P) : INT32_MAX;
+    for (int l = 0; l < LHF_SHAPE_LEVELS; l++) P->m2l_ns[l] = std::min(sh->m2l_tile[l], mx);
     P->p2p_ts = sh->p2p_tile;
     return LHF_OK;
 }
@@ -2008,8 +2012,7 @@ lhf_status lhf_plan_autotune(lhf_plan *P, const void *omega, const char *cache_p
     if (cache_path && cache_path[0] && read_shapes(cache_path, key, &sh, &lines)) {
         lhf_status s = lhf_plan_set_shapes(P, &sh);
         if (s != LHF_OK) return s;
-        if (out) *out = sh;
-        return LHF_OK;
+        return out ? lhf_plan_get_shapes(P, out) : LHF_OK;
     }
     P->stream = (hipStream_t)stream;
     int ns[MAXDEPTH + 1], ts = 0;

@@ -1,5 +1,5 @@
 """The file of tuned shapes names the M2L kernel that they were measured with: plans of one workload with other
-kernels, and entries without a name, do not share them."""
+kernels, and entries without a name, do not share them; and a plan reports the shapes that run."""
 import json
 
 import pytest
@@ -37,3 +37,16 @@ def test_kernels_do_not_share_shapes(tmp_path):
     plan = _plan(x)  # read back
     assert plan.autotune(w, cache_path=str(path)) == got["ROWS"] and len(json.loads(path.read_text())) == 4
     plan.close()
+
+
+def test_shapes_read_back_are_those_that_run():
+    import torch
+    import paper_1201_5430_amd as L
+    x, _ = workloads.vortex_ring(6000, 811)
+    x = torch.from_numpy(x).cuda()
+    ask = dict(m2l_tile=[0, 0, 6, 6, 4, 6, 1, 0, 0], p2p_tile=64)
+    for kw, mx in (({}, 5), (dict(m2l_kernel=L.M2L_QUARTER), 6)):
+        plan = _plan(x, **kw)
+        plan.set_shapes(ask)
+        assert plan.get_shapes() == dict(ask, m2l_tile=[min(t, mx) for t in ask["m2l_tile"]])
+        plan.close()
