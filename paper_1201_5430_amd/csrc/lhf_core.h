@@ -5,9 +5,11 @@
 // Up to u = 1 both come from polynomials in u.  Beyond, K = 1 - e^-u (erfcx(x) + 2 x / sqrt(pi)), x = sqrt u,
 // with erfcx(x) = e^(x^2) erfc(x) as a polynomial in 1 / (x + k), which maps the range to one where it is
 // nearly linear; no term cancels there (K >= 0.43).  The polynomials interpolate at Chebyshev nodes in
-// 70-digit arithmetic; relative errors: S, S' 1e-18 (FP64), 8e-9 and less (FP32), erfcx 4e-18 (FP64),
-// 6e-9 (FP32).  The library's erf and exp with their ranges took most of a pair's time: near field of
-// 2^20 uniform elements FP64 1.87 ms with them, 1.00 with these and the lanes split as k_p2p does.
+// 70-digit arithmetic, to relative 1e-18 (S, S') and 4e-18 (erfcx) in FP64, 5e-9 and less in FP32.  With the
+// coefficients rounded to the type, as they stand in the tables and enter the sums, evaluated exactly: FP64 S
+// 5.7e-17, S' 1.6e-16, erfcx 1.4e-16; FP32 S 1.0e-7, S' 7.2e-8, erfcx 2.0e-7, about a rounding of the type.
+// The library's erf and exp with their ranges took most of a pair's time: near field of
+// 2^20 uniform elements FP64 1.87 ms with them, 0.94 with these and the lanes split as k_p2p does.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -68,11 +70,12 @@ __device__ __forceinline__ double poly64(const double *p, double x)
     return r;
 }
 
-// e^-u, 0 <= u <= 46: e^-u = 2^n e^r, |r| <= ln 2 / 2, Taylor's polynomial
+// e^-u, 0 <= u <= 46: e^-u = 2^n e^r, |r| <= ln 2 / 2, Taylor's polynomial.  r by Cody and Waite's reduction:
+// ln 2 as a first part of 32 bits, whose product with n is exact, and the rest
 __device__ __forceinline__ double expm(double u)
 {
     const double n = rint(u * -1.4426950408889634074);
-    double r = fma(n, -6.93147180369123816490e-01, -u);  // ln 2 in two parts
+    double r = fma(n, -6.93147180369123816490e-01, -u);
     r = fma(n, -1.90821492927058770002e-10, r);
     const double p = poly64<14>(EXPM64, r);
     return ldexp(p, (int)n);
