@@ -216,7 +216,7 @@ __global__ void __launch_bounds__(256 * (tr::waves<T, P>()), (tr::waves<T, P>())
                         } else if constexpr (!SC && k >= q1 && k < q1 + R) {
                             tr::fmab<i / E>(o[R], cur[i % E], v[hoff(n0 + k - q1) + j]);
                         } else if constexpr (!SC && k >= q1 + R && k < q1 + 2 * R) {
-                            constexpr int r = k - q1 - R, n = n0 + r;
+                            constexpr int r = k - q1 - R;
                             if constexpr (r == 0) {
                                 settle();
                                 // phi: + i |d| m / n chi (the same m of the other potential)
@@ -224,7 +224,6 @@ __global__ void __launch_bounds__(256 * (tr::waves<T, P>()), (tr::waves<T, P>())
                             }
                             // chi_n - kappa chi_{n+1}
                             tr::fmab<i / E>(o[r], cur[i % E], wchi * o[r + 1]);
-                            (void)n;
                         }
                     });
                     __builtin_amdgcn_sched_barrier(0);
@@ -315,9 +314,9 @@ template <typename T, int P>
 hipError_t rows_attr()
 {
     const hipError_t e = hipFuncSetAttribute((const void *)k_m2l_rows<T, P, false>,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_CU);
     if (e != hipSuccess) return e;
-    return hipFuncSetAttribute((const void *)k_m2l_rows<T, P, true>, hipFuncAttributeMaxDynamicSharedMemorySize, 163840);
+    return hipFuncSetAttribute((const void *)k_m2l_rows<T, P, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_CU);
 }
 
 template <typename T, int P>

@@ -30,6 +30,10 @@
 #include "lhf_m2l_common.h"
 
 namespace lhf {
+
+constexpr int CUS = 256;           // compute units
+constexpr size_t LDS_CU = 163840;  // bytes of LDS of one
+
 namespace tn {
 
 // f(I), f(I + 1), .., f(N - 1) with the index as a type: arrays indexed by it stay in registers
@@ -337,7 +341,7 @@ inline size_t slot_bytes(int p, int npot) { return sizeof(double) * acc_stride(p
 template <typename T>
 inline int max_ns(int p, int npot)
 {
-    return (int)std::min<size_t>(60, (163840 - fixed_bytes<T>(p, npot)) / slot_bytes(p, npot));
+    return (int)std::min<size_t>(60, (LDS_CU - fixed_bytes<T>(p, npot)) / slot_bytes(p, npot));
 }
 inline int own_ns(const lhf_plan *Pl, int mx)
 {
@@ -392,6 +396,6 @@ void rows_launch(const lhf_plan *Pl, bool scalar, hipStream_t st);
 template <typename T, int P>
 hipError_t mm_rows_attr();
 template <typename T, int P>
-void mm_rows_launch(const lhf_plan *Pl, bool down, int l, bool add, hipStream_t st);
+void mm_rows_launch(const lhf_plan *Pl, bool down, int l, hipStream_t st);
 
 }  // namespace lhf

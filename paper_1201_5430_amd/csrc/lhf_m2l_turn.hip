@@ -404,7 +404,7 @@ int turn_own_ns(const lhf_plan *Pl) { return tr::own_ns(Pl, turn_max_ns(Pl)); }
 void mm_rows(const lhf_plan *Pl, bool down, int l, hipStream_t st)
 {
 #define F(N) \
-    if (Pl->p == N) return mm_rows_launch<T, N>(Pl, down, l, true, st);
+    if (Pl->p == N) return mm_rows_launch<T, N>(Pl, down, l, st);
     if (Pl->precision == LHF_FP64) {
         using T = double;
         LHF_TURN_FP64(F) LHF_ROWS_FP64(F)

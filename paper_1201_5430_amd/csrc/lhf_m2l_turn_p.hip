@@ -250,7 +250,7 @@ static void launch(const lhf_plan *Pl, hipStream_t st)
 {
     constexpr int NPOT = SC ? 1 : 2, WGS = tn::waves<T, P>();  // workgroups per compute unit
     constexpr size_t fixed = tn::fixed_bytes<T, P, NPOT>(), each = tn::slot_bytes<T, P, NPOT>();
-    const int mx = (int)std::min<size_t>(60, (163840 / WGS - fixed) / each);
+    const int mx = (int)std::min<size_t>(60, (LDS_CU / WGS - fixed) / each);
     int64_t nb = 0;
     for (int l = 2; l <= Pl->depth; l++) nb += Pl->lev[l].nb;
     const int ns = (int)std::max<int64_t>(1, std::min<int64_t>(mx, nb / (512 * WGS)));
@@ -264,7 +264,7 @@ static void launch(const lhf_plan *Pl, hipStream_t st)
 template <typename T, int P>
 hipError_t turn_attr()
 {
-    const int lds = 163840 / tn::waves<T, P>();
+    const int lds = LDS_CU / tn::waves<T, P>();
     const hipError_t e = hipFuncSetAttribute((const void *)k_m2l_turn<T, P, false>,
                                              hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;

@@ -24,8 +24,7 @@ template <typename T, int P, int KIND>
 __global__ void __launch_bounds__(256 * (tm::waves<T, P>()), (tm::waves<T, P>())) k_mm_rows(
     int64_t off, int64_t nb, const int32_t *__restrict__ bchild0, const int32_t *__restrict__ bnchild,
     const int32_t *__restrict__ bparent, const uint64_t *__restrict__ bkey, const T *__restrict__ src_exp,
-    T *__restrict__ dst_exp, const T *__restrict__ tab, const T *__restrict__ trig, const tn::Dir *__restrict__ dirs,
-    int add)
+    T *__restrict__ dst_exp, const T *__restrict__ tab, const T *__restrict__ trig, const tn::Dir *__restrict__ dirs)
 {
     static_assert(KIND == 0 || KIND == 2, "M2M or L2L");
     using tn::sfor;
@@ -271,9 +270,7 @@ __global__ void __launch_bounds__(256 * (tm::waves<T, P>()), (tm::waves<T, P>())
             using N0 = std::integral_constant<int, n0>;
             using N1 = std::integral_constant<int, n1>;
             T f[k + 1], g[k + 1];
-            if constexpr (KIND == 2) {
-                if (add) fetch(kk, gdst);
-            }
+            if constexpr (KIND == 2) fetch(kk, gdst);  // L2L adds to what the M2L wrote
             sfor<0, k + 1>([&](auto jj) {
                 constexpr int j = decltype(jj)::value;
                 f[j] = v[hoff(n0) + j];
@@ -332,7 +329,7 @@ __global__ void __launch_bounds__(256 * (tm::waves<T, P>()), (tm::waves<T, P>())
                     const int e = se + 4 * i;
                     if (4 * i + 3 < cnt || e < cnt) {
                         const T a = buf[(2 * st + sp) * BS + e] * sco[b0 + e];
-                        gdst[b0 + 4 * i] = add ? pre[i] + a : a;
+                        gdst[b0 + 4 * i] = pre[i] + a;
                     }
                 });
             }
@@ -341,23 +338,23 @@ __global__ void __launch_bounds__(256 * (tm::waves<T, P>()), (tm::waves<T, P>())
 }
 
 template <typename T, int P, int KIND>
-static void launch(const lhf_plan *Pl, int l, int add, hipStream_t st)
+static void launch(const lhf_plan *Pl, int l, hipStream_t st)
 {
     constexpr int NW = 4 * tm::waves<T, P>();
     const int64_t nb = Pl->lev[l].nb, nwork = KIND == 0 ? nb : (nb + 7) / 8;
     if (nb == 0) return;
-    // one pass over the tables per workgroup: as many as the chip holds at a time
-    const unsigned grid = (unsigned)std::min<int64_t>((nwork + NW - 1) / NW, 256 * (163840 / tm::bytes<T, P>()));
+    // one pass over the tables per workgroup: as many as the chip (CUS compute units of LDS_CU bytes) holds
+    const unsigned grid = (unsigned)std::min<int64_t>((nwork + NW - 1) / NW, CUS * (LDS_CU / tm::bytes<T, P>()));
     k_mm_rows<T, P, KIND><<<dim3(grid), dim3(64 * NW), tm::bytes<T, P>(), st>>>(
         Pl->lev[l].off, nb, Pl->bchild0, Pl->bnchild, Pl->bparent, Pl->bkey,
         (const T *)(KIND == 0 ? Pl->M : Pl->Lc), (T *)(KIND == 0 ? Pl->M : Pl->Lc), (const T *)Pl->mmtab,
-        (const T *)Pl->ttrig, (const tn::Dir *)Pl->tdir, add);
+        (const T *)Pl->ttrig, (const tn::Dir *)Pl->tdir);
 }
 
 template <typename T, int P>
 hipError_t mm_rows_attr()
 {
-    static_assert(tm::bytes<T, P>() <= 163840, "tables and stretches exceed the LDS");
+    static_assert(tm::bytes<T, P>() <= LDS_CU, "tables and stretches exceed the LDS");
     const hipError_t e = hipFuncSetAttribute((const void *)k_mm_rows<T, P, 0>,
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)tm::bytes<T, P>());
     if (e != hipSuccess) return e;
@@ -367,13 +364,13 @@ hipError_t mm_rows_attr()
 
 // M2M into the boxes of level l, or L2L into them from level l - 1 (l >= 3), added to what they hold
 template <typename T, int P>
-void mm_rows_launch(const lhf_plan *Pl, bool down, int l, bool add, hipStream_t st)
+void mm_rows_launch(const lhf_plan *Pl, bool down, int l, hipStream_t st)
 {
-    if (down) launch<T, P, 2>(Pl, l, add, st);
-    else launch<T, P, 0>(Pl, l, 0, st);
+    if (down) launch<T, P, 2>(Pl, l, st);
+    else launch<T, P, 0>(Pl, l, st);
 }
 
 template hipError_t mm_rows_attr<LHF_TURN_T, LHF_TURN_P>();
-template void mm_rows_launch<LHF_TURN_T, LHF_TURN_P>(const lhf_plan *, bool, int, bool, hipStream_t);
+template void mm_rows_launch<LHF_TURN_T, LHF_TURN_P>(const lhf_plan *, bool, int, hipStream_t);
 
 }  // namespace lhf
