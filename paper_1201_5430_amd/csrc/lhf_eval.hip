@@ -1433,6 +1433,63 @@ __global__ void __launch_bounds__(NT) k_p2p(int64_t n, int depth, int64_t leaf_o
     }
 }
 
+// uniform tree, sparse: one lane per sorted element over the 27 adjacent leaves, sums of one leaf's pairs in
+// compensated accumulators.  Where the leaves hold an element or two, a workgroup's barriers and the empty
+// lanes of k_p2p cost more than the pairs (p2p_sparse).
+template <typename T, bool GRAD, bool Q>
+__global__ void __launch_bounds__(256) k_p2p_lane(int64_t n, int depth, int64_t leaf_off, const int32_t *__restrict__ eleaf,
+                                                  const int32_t *__restrict__ ulist, const uint64_t *__restrict__ bkey,
+                                                  const int32_t *__restrict__ bstart, const int32_t *__restrict__ bcount,
+                                                  const T *__restrict__ xw, const double *__restrict__ sys_a, int what,
+                                                  const T *__restrict__ vfar, const int32_t *__restrict__ perm,
+                                                  T *__restrict__ vout, T *__restrict__ sout, T *__restrict__ gout,
+                                                  T *__restrict__ bout)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    constexpr int NA = GRAD ? 15 : 6;
+    const int lf = eleaf[i];
+    const T a = (T)sys_a[bkey[lf] >> (3 * depth)];  // core radius of the element's system (0: singular kernel)
+    const int smooth = a > (T)0;
+    const Rec<T> me = load_rec<false>(xw, (int)i);
+    CompSum<T> acc[NA];
+    if (what & 1)
+        for (int k = 0; k < NA; k++) acc[k].add(vfar[(size_t)k * n + i]);
+    const int32_t *U = ulist + (size_t)(lf - leaf_off) * 27;
+    for (int q = 0; q < 27 && (what & 2); q++) {
+        const int nb = U[q];
+        if (nb < 0) continue;
+        const int st = bstart[nb], en = st + bcount[nb];
+        T part[NA];
+#pragma unroll
+        for (int k = 0; k < NA; k++) part[k] = 0;
+        for (int e = st; e < en; e++) {
+            if (e == (int)i) continue;
+            const Rec<T> r = load_rec<Q>(xw, e);
+            if constexpr (GRAD) p2p_pair_grad<T, Q>(r, me.x, me.y, me.z, me.wx, me.wy, me.wz, a, smooth, part);
+            else
+                p2p_pair<T, Q>(r, me.x, me.y, me.z, me.wx, me.wy, me.wz, a, smooth, part[0], part[1], part[2], part[3],
+                               part[4], part[5]);
+        }
+#pragma unroll
+        for (int k = 0; k < NA; k++) acc[k].add(part[k]);
+    }
+    const int64_t o = perm[i];
+    for (int k = 0; k < 3; k++) {
+        vout[3 * o + k] = acc[k].value();
+        sout[3 * o + k] = acc[3 + k].value();
+    }
+    if constexpr (GRAD) {
+        T b = 0;
+        for (int k = 0; k < 9; k++) {
+            const T gk = acc[6 + k].value();
+            if (gout) gout[9 * o + k] = gk;
+            b += gk * gk;
+        }
+        if (bout) bout[o] = b;  // beta = grad v : grad v
+    }
+}
+
 // adaptive tree: near field of one target leaf per workgroup of NT lanes, then combination with the
 // far field and un-permutation.  The leaf's source list (U-list leaves with the smoothed kernel,
 // then W/X boxes with the singular one) is staged through LDS in tiles of P2P_TS element records,
@@ -1784,16 +1841,33 @@ __global__ void k_gather_w(int64_t n, const T *__restrict__ w, const T *__restri
 }
 
 // Four wavefronts a leaf instead of one where the leaves are too few to fill the chip's 1024 SIMDs with
-// eight wavefronts each (near field of 4,096 elements 19 us with four, 49 with one; 65,537 at depth 4
-// 199, 298), and, as long as the leaves alone don't, where they hold eight elements and more: the fullest
-// leaves would end last (ring of 400,003, 16 a leaf: 4.5 ms, 10.1; of 100,003 with gradient: 1.6, 3.8;
+// eight wavefronts each, if they hold enough for four: six elements (near field FP64 in 4,096 leaves: 8 a leaf
+// 67 us with four, 94 with one; 3.1 a leaf 51, 24; adaptive 4,065 leaves of 4.9 101, 57), and from four on where
+// they are fewer still and latency is all (64 leaves: 6.3 a leaf 17, 26; 3.2 a leaf 18, 14).  As long as the leaves
+// alone don't fill the chip, also where they hold eight elements and more: the fullest
+// leaves would end last (ring of 400,003, 16 a leaf: 4.5 ms, 10.1;
 // 56,000 leaves of a batch, 68 each: 16.8 ms for the whole call, 20.8).  Else one: 2^20 elements in
 // 262,144 leaves of four 1.00 ms with one, 2.45 with four; ring of 4.2 million, 16 a leaf, 18.5, 20.8.
-constexpr int64_t P2P_FEW = 8192, P2P_MANY = 131072;
+constexpr int64_t P2P_FEWEST = 1024, P2P_FEW = 8192, P2P_MANY = 131072;
 
 static bool p2p_wide(const lhf_plan *P)
 {
-    return P->nleaf < P2P_FEW || (P->nleaf < P2P_MANY && P->n >= 8 * P->nleaf);
+    const int each = P->nleaf < P2P_FEWEST ? 4 : P->nleaf < P2P_FEW ? 6 : 8;
+    return P->nleaf < P2P_MANY && P->n >= each * P->nleaf;
+}
+
+// A lane per target instead of a leaf per workgroup, on uniform trees without full leaves (a lane walks all
+// sources of its target): where many leaves hold an element or two (a workgroup takes about 1.8 ns of the
+// chip; near field FP64, lane and leaf: 58,000 leaves of 1.13 71, 121 us; 165,000 of 1.6 231, 311; 205,000 of 1.95
+// 379, 392, FP32 172, 211; 227,000 of 2.3 487, 460, but FP32 226, 238 and with gradient 597, 630; 244,000 of 2.9
+// 713, 591, FP32 318, 290; 20,700 of 1.6 115, 48), and where nearly all neighbours are empty (20,000 elements at
+// depth 8 19, 43; 262,144 62, 446).
+template <typename T, bool GRAD>
+static bool p2p_sparse(const lhf_plan *P)
+{
+    if (P->adaptive || P->fullest > 256) return false;
+    const int most = GRAD || sizeof(T) == 4 ? 10 : 9;  // quarters of an element per leaf
+    return (P->nleaf >= 32768 && 4 * P->n < most * P->nleaf) || 8 * P->n_p2p < P->n;
 }
 
 // Workgroups that share a leaf's targets, 64 at a time (uniform trees; adaptive ones bound their leaves): as many
@@ -1839,6 +1913,12 @@ template <typename T, bool GRAD, bool Q>
 static void p2p_launch(lhf_plan *P, int what, T *v, T *s, T *g, T *b, hipStream_t st)
 {
     if (P->nleaf == 0) return;
+    if (p2p_sparse<T, GRAD>(P)) {
+        hipLaunchKernelGGL((k_p2p_lane<T, GRAD, Q>), dim3((unsigned)((P->n + 255) / 256)), dim3(256), 0, st, P->n,
+                           P->depth, P->lev[P->depth].off, P->eleaf, P->ulist, P->bkey, P->bstart, P->bcount,
+                           (const T *)P->xw, P->sys_a, what, (const T *)P->vfar, P->perm, v, s, g, b);
+        return;
+    }
     if (p2p_wide(P)) p2p_launch_t<T, GRAD, Q, 256>(P, what, v, s, g, b, st);
     else p2p_launch_t<T, GRAD, Q, 64>(P, what, v, s, g, b, st);
 }

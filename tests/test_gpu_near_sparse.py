@@ -1,0 +1,74 @@
+"""Near field of trees whose leaves hold an element or two: against the oracle on both sides of the line between
+a lane per target and a workgroup per leaf, and times that must not grow where the work shrinks.
+
+Bars: those of the other comparisons with the oracle."""
+import numpy as np
+import pytest
+
+from parity_util import check, check32
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("full", [False, True], ids=["v s", "grad q"])
+@pytest.mark.parametrize("n,depth,clump", [(1, 4, 0), (600, 6, 0), (600, 8, 0), (600, 6, 300), (40000, 6, 0),
+                                           (40000, 6, 100), (40000, 6, 300)])
+def test_sparse(oracle, prec, full, n, depth, clump):
+    import torch
+    import paper_1201_5430_amd as L
+    rng = np.random.default_rng(500 + n + clump)
+    x = np.concatenate([rng.uniform(0, 1, (n, 3)), (5 + rng.uniform(0.1, 0.9, (clump, 3))) / 2 ** depth])
+    w, q, a = rng.normal(size=x.shape), rng.normal(size=len(x)), 0.004
+    dt = torch.float64 if prec == 0 else torch.float32
+    if prec:
+        x, w, q = (u.astype(np.float32).astype(np.float64) for u in (x, w, q))
+        a = float(np.float32(a))
+    xt, wt, qt = (torch.from_numpy(u).to("cuda", dt) for u in (x, w, q))
+    plan = L.Plan(xt, a, p=4, depth=depth, precision=prec, grad=full)
+    out = plan.execute(wt, what=2, q=qt if full else None, grad=full, beta=full)
+    torch.cuda.synchronize()
+    plan.close()
+    ref = oracle.fmm(x, w, a, 4, depth, far=False, q=q if full else None, grad=full)
+    out = [t.double().cpu().numpy() for t in out]
+    if n == 1 and not clump:
+        assert not any(np.any(t) for t in out)
+        return
+    chk = check if prec == 0 else check32
+    chk(out[0], out[1], ref[0], ref[1], label=f"sparse n={n} depth={depth} clump={clump} prec={prec}:")
+    if full:
+        chk(out[2], out[2], ref[2], ref[2], label="  grad v:")
+        g = out[2].reshape(len(x), 9)
+        assert np.allclose(out[3], (g * g).sum(1), rtol=1e-12 if prec == 0 else 1e-5)
+
+
+def _us(n, dt, depth, grad, mpl=0):
+    import torch
+    import paper_1201_5430_amd as L
+    rng = np.random.default_rng(510)
+    x = torch.from_numpy(rng.uniform(0, 1, (n, 3))).to("cuda", dt).clamp(max=1 - 2.0 ** -24)
+    w = torch.from_numpy(rng.normal(size=(n, 3))).to("cuda", dt)
+    plan = L.Plan(x, 0.5 * n ** (-1 / 3), p=4, depth=depth, precision=0 if dt == torch.float64 else 1, grad=grad,
+                  max_per_leaf=mpl)
+    best = float("inf")
+    for k in range(10):
+        plan.profile_begin(1)
+        plan.execute(w, what=2, grad=grad)
+        best = min(best, plan.profile_end()[0]["p2p"] * 1e3) if k > 1 else best
+    plan.close()
+    return best
+
+
+@pytest.mark.parametrize("grad", [False, True])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_less_work_takes_less_time(prec, grad):
+    import torch
+    dt = torch.float64 if prec == 0 else torch.float32
+    # the same elements without neighbours (before: 1.1 to 1.4 times the time of those with 13 each)
+    t = [_us(131072, dt, d, grad) for d in (6, 8)]
+    print(f"131072 elements prec={prec} grad={grad}: depth 6 {t[0]:.0f} us, depth 8 {t[1]:.0f} us", flush=True)
+    assert t[1] <= 0.75 * t[0], t
+    # a fifth of the elements in single-element leaves of an adaptive tree (before: 0.9 to 1.1 times)
+    t = [_us(n, dt, 8, grad, mpl=1) for n in (20000, 4000)]
+    print(f"adaptive prec={prec} grad={grad}: 20000 {t[0]:.0f} us, 4000 {t[1]:.0f} us", flush=True)
+    assert t[1] <= 0.85 * t[0], t
