@@ -47,7 +47,8 @@ if ROOT not in sys.path:
 METRIC = "vortex elements/s (v + stretching) at rel err 1e-6; FP32-MFMA vs FP64 speedup"
 P_STAR = 23  # smallest p with eps2(v), eps2(s) <= 1e-6 on the ring (error-vs-order sweep)
 PEAK_FP64_TFLOPS = 78.6          # 256 CU x 4 SIMD x 16 lanes x 2 flop x 2.4 GHz (vector and matrix)
-PEAK_FP32_VALU_TFLOPS = 78.6     # non-packed FP32 FMA: the same unit count (the build forbids packed FP32)
+# non-packed FP32 FMA (the build forbids packed FP32): one per 2.2 cycles of a SIMD with two wavefronts, measured
+PEAK_FP32_VALU_TFLOPS = 157.3
 PEAK_FP32_MFMA_TFLOPS = 157.3    # FP32 matrix cores
 PEAK_HBM_GBS = 8000.0
 

@@ -361,8 +361,11 @@ extern "C" {
 void lhf_tune_default(int32_t p, int32_t precision, lhf_tune *t)
 {
     if (!t) return;
-    // unit costs measured with this library on MI355X (uniform cubes, FP32 at p = 10,
-    // FP64 at p = 12), scaled to other p by the p^3 work of a rotation-based M2L
+    // unit costs of an earlier state of the kernels on MI355X (uniform cubes, FP32 at p = 10, FP64 at
+    // p = 12), scaled to other p by the p^3 work of a rotation-based M2L.  They stay: the depth decides which
+    // pairs are summed directly, and with that the result.  lhf_autotune measures the present kernels (FP32
+    // p = 10: 52 ns a box, 0.0019 a pair); batch of 256 systems FP32, tuned and by these costs: p = 8 16.4,
+    // 16.3 ms, p = 10 17.6, 16.8, p = 12 19.3, 20.0, p = 16 26.5, 30.0
     const double q = (double)p * p * p;
     t->p = p;
     t->precision = precision;

@@ -95,7 +95,7 @@ __device__ inline void box_centre(uint64_t key, int level, const double *__restr
 // once per leaf, to the sums of the pairs around (n, m), instead of once per element (twelve LDS reads and
 // some sixty operations).  The columns are stored as triangles (n, m <= n).
 // P2M before and now: ring of 4.2 million, FP64 p = 23 14.1 -> 6.0 ms; 2^20 segments of filaments, p = 12 10.9
-// -> 4.0 ms; 2^20 elements, p = 12 1.5 -> 1.2 ms.  The harmonics' recurrences bound it now.
+// -> 4.0 ms; 2^20 elements, p = 12 1.5 -> 1.1 ms.  The harmonics' recurrences bound it now.
 // ---------------------------------------------------------------------------
 // SC: scalar harmonic FMM -- phi = sum q g_n^m (the expansion of eq. rsbf5 of each source), chi = 0.
 // SEG: vortex filaments -- each element is a segment (centre x, vector sl) expanded as nq

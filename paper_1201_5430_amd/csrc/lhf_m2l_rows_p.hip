@@ -15,6 +15,10 @@
 // The turn's and the shift's matrix entries are the same for all 16 lanes of a row: a row's next 16 or
 // 32 entries are one LDS load, and the multiplications broadcast them from the loaded register
 // (row_newbcast), so LDS returns 1/16 of what a broadcast read for each multiplication would.
+// What bounds it (4M ring at p = 23, one wavefront per SIMD, 256 VGPRs + 256 AGPRs, no scratch; counters in
+// profiles/): vector instructions are in flight 58% of a wavefront's cycles, 66% of them FMAs; it waits 19% of them,
+// 8% on LDS, where accumulations and angles conflict.  HBM 102 GB in 237 ms, 5% of the peak.  p = 13 (two
+// wavefronts): vector issue 53% of the time, waits 32%, LDS 12%.
 #include <algorithm>
 
 #include "lhf_m2l_turn.h"

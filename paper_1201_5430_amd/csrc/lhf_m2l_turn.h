@@ -16,9 +16,9 @@
 // time, which therefore need no LDS read per multiplication.  The M2L of every level is one launch.
 //
 // M2L per execute on MI355X, before (half- and quarter-vector kernels, per-box kernel at other orders)
-// and now: 2^20 cube FP64 p = 12 48.1 -> 33.2 ms, FP32 p = 10 23.5 -> 11.5 ms; 4M ring FP64 p = 23
-// 381 -> 237 ms, FP64 p = 16 114 -> 77 ms, FP32 p = 16 101 -> 48 ms; 131,101 elements at depth 5, FP64
-// p = 13 142 -> 6.9 ms.
+// and now: 2^20 cube FP64 p = 12 48.0 -> 33.0 ms, FP32 p = 10 23.5 -> 10.2 ms; 4M ring FP64 p = 23
+// 381 -> 237 ms, FP64 p = 16 114 -> 76 ms, FP32 p = 16 101 -> 46 ms; 131,101 elements at depth 5, FP64
+// p = 13 143 -> 7.4 ms.
 #pragma once
 
 #include <hip/hip_runtime.h>

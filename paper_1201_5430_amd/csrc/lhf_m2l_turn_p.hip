@@ -9,9 +9,10 @@
 // chunk's multiplications and waited for after them (volatile loads: as plain ones the compiler places
 // them behind the multiplications; FP64 p = 12 on the 2^20 cube 47.6 -> 41 ms with the request ahead, and
 // 33 ms with outputs as the inner loop, which keeps neighbouring multiplications independent).
-// What bounds it (FP64 p = 12, one wavefront per SIMD: 256 VGPRs + 256 AGPRs): the vector unit issues 43%
-// of the time, waits for scalar loads and LDS are 32%; FP32 and FP64 p = 8 (two or more wavefronts) also
-// the source loads (64 lines an instruction) and LDS (angles, accumulation).
+// What bounds it (FP64 p = 12, 2^20 cube, one wavefront per SIMD: 256 VGPRs + 256 AGPRs, 100 bytes of scratch a
+// lane; counters in profiles/): the vector unit issues 52% of the time, 58% of that FMAs; a wavefront waits 18%
+// of its cycles for scalar loads, LDS and sources, and 12% to issue.  FP32 and FP64 p = 8 (two or more
+// wavefronts): also the source loads (64 lines an instruction) and LDS (angles, accumulation).
 #include <algorithm>
 
 #include "lhf_m2l_turn.h"

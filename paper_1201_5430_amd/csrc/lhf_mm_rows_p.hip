@@ -11,8 +11,9 @@
 //
 // What bounded the kernels before: table reads, one 16-byte load per two multiplications (the classes'
 // tables in LDS or, from p = 20 on, in the caches), and for other orders a serial per-box kernel.
-// M2M before and now: ring of 4.2 million at FP64 p = 23 15.4 -> 4.1 ms (L2L 14.4 ms -> 5.4 ms together with
-// the M2L's source copy), 65,537 elements at p = 18 1.27 -> 0.06 ms (L2L 0.24 -> 0.08 ms).
+// M2M before and now: ring of 4.2 million at FP64 p = 23 15.4 -> 4.1 ms (L2L with the M2L's source copy 13.2 ->
+// 5.0), 65,537 elements at p = 18 1.27 -> 0.06 ms.  What bounds it there: waits for memory and LDS, 64% of a
+// wavefront's cycles (one per SIMD; 796 and 816 bytes of scratch a lane); the vector unit issues 20% of the time.
 #include <algorithm>
 
 #include "lhf_m2l_turn.h"

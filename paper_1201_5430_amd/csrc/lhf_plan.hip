@@ -1497,8 +1497,9 @@ static const char *m2l_name(int k)
 }
 
 // Resolve the descriptor's kernel requests (host only, before any launch).  AUTO takes the
-// fastest kernel measured for (precision, p): the quarter-vector kernel at FP64 p >= 16, the
-// half-vector kernel where it is instantiated, else the one-lane tile, else the generic per-box
+// fastest kernel measured for (precision, p) beside those by quarter turns, which plan_new puts in its
+// place where they run: the quarter-vector kernel at FP64 p >= 16, the half-vector kernel where it is
+// instantiated, else the one-lane tile, else the generic per-box
 // kernel; with LHF_DETERMINISTIC only kernels
 // without atomics qualify (then the matrix-core kernel, which is deterministic, precedes the
 // generic one).  Batched kernels need the dense box maps: depth <= 8 and at most 2^28 cells.
