@@ -1844,15 +1844,20 @@ __global__ void k_gather_w(int64_t n, const T *__restrict__ w, const T *__restri
 // eight wavefronts each, if they hold enough for four: six elements (near field FP64 in 4,096 leaves: 8 a leaf
 // 67 us with four, 94 with one; 3.1 a leaf 51, 24; adaptive 4,065 leaves of 4.9 101, 57), and from four on where
 // they are fewer still and latency is all (64 leaves: 6.3 a leaf 17, 26; 3.2 a leaf 18, 14).  As long as the leaves
-// alone don't fill the chip, also where they hold eight elements and more: the fullest
+// alone don't fill the chip, also where they hold ten elements and more: the fullest
 // leaves would end last (ring of 400,003, 16 a leaf: 4.5 ms, 10.1;
-// 56,000 leaves of a batch, 68 each: 16.8 ms for the whole call, 20.8).  Else one: 2^20 elements in
+// 56,000 leaves of a batch, 68 each: 16.8 ms for the whole call, 20.8), even ones win little (32,768 uniform leaves:
+// 8 a leaf 423 us, 370, 12 a leaf 764, 786), FP64 with gradients from twelve on (8 a leaf 561, 445; 11 a leaf in an
+// adaptive tree 2.54 ms, 2.27) and gradients not in adaptive trees with leaves of one size (24 a leaf 4.92, 4.07).  Else one: 2^20 elements in
 // 262,144 leaves of four 1.00 ms with one, 2.45 with four; ring of 4.2 million, 16 a leaf, 18.5, 20.8.
 constexpr int64_t P2P_FEWEST = 1024, P2P_FEW = 8192, P2P_MANY = 131072;
 
+template <typename T, bool GRAD>
 static bool p2p_wide(const lhf_plan *P)
 {
-    const int each = P->nleaf < P2P_FEWEST ? 4 : P->nleaf < P2P_FEW ? 6 : 8;
+    const int each = P->nleaf < P2P_FEWEST ? 4 : P->nleaf < P2P_FEW ? 6 : GRAD && sizeof(T) == 8 ? 12 : 10;
+    // leaves of one size have no W or X pair
+    if (GRAD && P->adaptive && P->nleaf >= P2P_FEW && P->n_wx + P->n_m2p + P->n_p2l == 0) return false;
     return P->nleaf < P2P_MANY && P->n >= each * P->nleaf;
 }
 
@@ -1919,7 +1924,7 @@ static void p2p_launch(lhf_plan *P, int what, T *v, T *s, T *g, T *b, hipStream_
                            (const T *)P->xw, P->sys_a, what, (const T *)P->vfar, P->perm, v, s, g, b);
         return;
     }
-    if (p2p_wide(P)) p2p_launch_t<T, GRAD, Q, 256>(P, what, v, s, g, b, st);
+    if (p2p_wide<T, GRAD>(P)) p2p_launch_t<T, GRAD, Q, 256>(P, what, v, s, g, b, st);
     else p2p_launch_t<T, GRAD, Q, 64>(P, what, v, s, g, b, st);
 }
 
